@@ -374,6 +374,7 @@ hipError_t launch_permute(int elem_bytes, const void* in, void* out, int rank, c
 // inner loop is two LDS reads and two gathered loads per term.
 
 constexpr int kTabBits = 10;
+constexpr int kGenericLanesLog2 = 16;  // threads that the lanes form fills at most
 
 template <typename E>
 __global__ __launch_bounds__(256) void k_generic(const E* __restrict__ A, const E* __restrict__ B,
@@ -415,6 +416,70 @@ __global__ __launch_bounds__(256) void k_generic(const E* __restrict__ A, const 
   record_max(maxslot, mx);
 }
 
+// Few outputs: 2^L consecutive lanes of a wave share one output, lane t taking
+// the terms t, t + 2^L, ..., and add their sums by butterfly.  With one
+// output per thread a step of 2^7 outputs over 2^11 terms was 128 serial
+// chains of dependent gathers (359 us, 18 us now).  A lane's terms are
+// gathered four at a time; the offsets of its first kGenTab / 2^L terms per
+// operand come from an LDS table as in k_generic.
+template <typename E>
+__global__ __launch_bounds__(256) void k_generic_lanes(const E* __restrict__ A, const E* __restrict__ B,
+                                                      E* __restrict__ C, const IndexOp op, int L, float* maxslot) {
+  __shared__ uint64_t atab[1 << kTabBits], btab[1 << kTabBits];
+  const int lo_bits = op.nK < kTabBits ? op.nK : kTabBits;
+  const int n_lo = 1 << lo_bits;
+  for (int k = threadIdx.x; k < n_lo; k += blockDim.x) {
+    atab[k] = dep((uint64_t)k, op.aK);
+    btab[k] = dep((uint64_t)k, op.bK);
+  }
+  __syncthreads();
+  const int64_t nT = (int64_t)1 << (op.nM + op.nN + L);
+  const int64_t n_hi = (int64_t)1 << (op.nK - lo_bits);
+  const uint64_t nmask = (1ull << op.nN) - 1ull;
+  const int t = threadIdx.x & ((1 << L) - 1);
+  float mx = 0.f;
+  // (the thread count is a multiple of whole outputs, so the lanes of an
+  // output are in or out of the loop together)
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < nT; i += (int64_t)gridDim.x * 256) {
+    const uint64_t c = (uint64_t)i >> L;
+    const uint64_t m = c >> op.nN, n = c & nmask;
+    const uint64_t ab = dep(m, op.aM), bb = dep(n, op.bN);
+    float re = 0.f, im = 0.f;
+    for (int64_t h = 0; h < n_hi; ++h) {
+      const E* Ah = A + (ab | dep((uint64_t)h << lo_bits, op.aK));
+      const E* Bh = B + (bb | dep((uint64_t)h << lo_bits, op.bK));
+      float pr = 0.f, pi = 0.f;
+      auto madd = [&](const float2 x, const float2 y) {
+        pr = fmaf(x.x, y.x, pr);
+        pr = fmaf(-x.y, y.y, pr);
+        pi = fmaf(x.x, y.y, pi);
+        pi = fmaf(x.y, y.x, pi);
+      };
+      int k = t;
+      for (; k + (3 << L) < n_lo; k += 4 << L) {
+        float2 x[4], y[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          x[q] = to_f2(Ah[atab[k + (q << L)]]);
+          y[q] = to_f2(Bh[btab[k + (q << L)]]);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) madd(x[q], y[q]);
+      }
+      for (; k < n_lo; k += 1 << L) madd(to_f2(Ah[atab[k]]), to_f2(Bh[btab[k]]));
+      re += pr;
+      im += pi;
+    }
+    for (int o = 1 << (L - 1); o > 0; o >>= 1) {
+      re += __shfl_xor(re, o);
+      im += __shfl_xor(im, o);
+    }
+    mx = mag_max(mx, re, im);
+    if (t == 0) C[c] = from_f2<E>(re * op.out_scale, im * op.out_scale);
+  }
+  record_max(maxslot, mx);
+}
+
 // Short sums into many outputs (2^nM, 2^nN >= 64, 2^nK <= 16): a workgroup
 // owns a 64 x 64 output tile, gathers the tile's A rows (64 x 2^nK) and B
 // rows once into LDS in FP32, and each thread accumulates a 4 x 4 block of
@@ -426,14 +491,30 @@ __global__ __launch_bounds__(256) void k_generic_tiled(const E* __restrict__ A, 
   const int nk = 1 << op.nK;
   const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
   const int64_t tiles_n = (int64_t)1 << (op.nN - 6), tiles = (int64_t)1 << (op.nM + op.nN - 12);
+  // this thread gathers row r of both operands at k = kq, kq + 4, ...
+  const int r = tid & 63, kq = tid >> 6;
+  const uint64_t ar = dep((uint64_t)r, op.aM), br = dep((uint64_t)r, op.bN);
+  uint64_t ak[4], bk[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    ak[q] = bk[q] = 0;
+    if (4 * q < nk) {
+      ak[q] = ar | dep((uint64_t)(kq + 4 * q), op.aK);
+      bk[q] = br | dep((uint64_t)(kq + 4 * q), op.bK);
+    }
+  }
   float mx = 0.f;
   for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
     const int64_t m0 = (t / tiles_n) << 6, n0 = (t % tiles_n) << 6;
-    for (int i = tid; i < 64 * nk; i += 256) {
-      const int k = i >> 6, r = i & 63;
-      const uint64_t ak = dep((uint64_t)k, op.aK), bk = dep((uint64_t)k, op.bK);
-      As[k][r] = to_f2(A[dep((uint64_t)(m0 + r), op.aM) | ak]);
-      Bs[k][r] = to_f2(B[dep((uint64_t)(n0 + r), op.bN) | bk]);
+    const E* At = A + dep((uint64_t)m0, op.aM);
+    const E* Bt = B + dep((uint64_t)n0, op.bN);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int k = kq + 4 * q;
+      if (k < nk) {
+        As[k][r] = to_f2(At[ak[q]]);
+        Bs[k][r] = to_f2(Bt[bk[q]]);
+      }
     }
     __syncthreads();
     float re[4][4], im[4][4];
@@ -483,6 +564,22 @@ hipError_t launch_generic(int dtype, const void* A, const void* B, void* C, cons
     else
       hipLaunchKernelGGL(k_generic_tiled<float2>, g, dim3(256), 0, s, (const float2*)A, (const float2*)B,
                          (float2*)C, op, maxslot);
+    return hipGetLastError();
+  }
+  // several lanes per output while the outputs alone leave CUs without
+  // threads (2^16 threads, one block per CU) and the sum has terms for them
+  const int lanes = std::min({6, op.nK, kGenericLanesLog2 - (op.nM + op.nN)});
+  if (lanes > 0) {
+    const dim3 g((unsigned)std::max<int64_t>(1, (int64_t)1 << std::max(0, op.nM + op.nN + lanes - 8)));
+    if (dtype == TN_DTYPE_F16S)
+      hipLaunchKernelGGL(k_generic_lanes<cf16>, g, dim3(256), 0, s, (const cf16*)A, (const cf16*)B, (cf16*)C, op,
+                         lanes, maxslot);
+    else if (dtype == TN_DTYPE_BF16S)
+      hipLaunchKernelGGL(k_generic_lanes<cbf16>, g, dim3(256), 0, s, (const cbf16*)A, (const cbf16*)B, (cbf16*)C, op,
+                         lanes, maxslot);
+    else
+      hipLaunchKernelGGL(k_generic_lanes<float2>, g, dim3(256), 0, s, (const float2*)A, (const float2*)B,
+                         (float2*)C, op, lanes, maxslot);
     return hipGetLastError();
   }
   const int64_t nC = (int64_t)1 << (op.nM + op.nN);
@@ -821,13 +918,20 @@ __global__ __launch_bounds__(256) void k_splitk_part(const E* __restrict__ A, co
   }
 }
 
+// Sums the block partials of group blockIdx.x.  Thread (slice, output): the
+// outputs are consecutive threads, so a slice reads whole runs of partials;
+// 1024 / nout slices take the blocks in turn, then add up in a fixed tree.
+// (Summed output after output by 256 threads, 64 outputs of 512 blocks took
+// 70 us; 6 us now.)
+constexpr int kFinalThreads = 1024;
+
 template <typename E>
-__global__ __launch_bounds__(256) void k_splitk_final(const float2* __restrict__ part, int nblk, int nout,
-                                                     E* __restrict__ C, float out_scale, float* maxslot, int ln_sub,
-                                                     int ln_row, int lm_sub, int gn_bits) {
-  __shared__ float red[2][256];
-  const int tid = threadIdx.x;
-  float mx = 0.f;
+__global__ __launch_bounds__(kFinalThreads) void k_splitk_final(const float2* __restrict__ part, int nblk, int ln_out,
+                                                               E* __restrict__ C, float out_scale, float* maxslot,
+                                                               int ln_sub, int ln_row, int lm_sub, int gn_bits) {
+  __shared__ float2 red[kFinalThreads];
+  const int tid = threadIdx.x, nout = 1 << ln_out;
+  const int o = tid & (nout - 1), slice = tid >> ln_out, slices = kFinalThreads >> ln_out;
   {
     // group blockIdx.x = (im, in): its block partials, and its outputs'
     // first row and column in C
@@ -836,31 +940,29 @@ __global__ __launch_bounds__(256) void k_splitk_final(const float2* __restrict__
     const int64_t im = grp >> gn_bits, in = grp & ((1 << gn_bits) - 1);
     C += ((im << lm_sub) << ln_row) | (in << ln_sub);
   }
-  for (int o = 0; o < nout; ++o) {
-    float r = 0.f, i = 0.f;
-    for (int g = tid; g < nblk; g += 256) {
-      const float2 v = part[(int64_t)g * nout + o];
-      r += v.x;
-      i += v.y;
-    }
-    red[0][tid] = r;
-    red[1][tid] = i;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-      if (tid < w) {
-        red[0][tid] += red[0][tid + w];
-        red[1][tid] += red[1][tid + w];
-      }
-      __syncthreads();
-    }
-    if (tid == 0) {
-      mx = mag_max(mx, red[0][0], red[1][0]);
-      // output o = (i, j) of the group (j < 2^ln_sub) sits at row i, column j
-      // of C, whose rows hold 2^ln_row entries
-      C[((int64_t)(o >> ln_sub) << ln_row) | (o & ((1 << ln_sub) - 1))] =
-          from_f2<E>(red[0][0] * out_scale, red[1][0] * out_scale);
+  float r = 0.f, i = 0.f;
+#pragma unroll 8
+  for (int g = slice; g < nblk; g += slices) {
+    const float2 v = part[((int64_t)g << ln_out) | o];
+    r += v.x;
+    i += v.y;
+  }
+  red[tid] = make_float2(r, i);
+  __syncthreads();
+  for (int w = slices >> 1; w > 0; w >>= 1) {
+    if (slice < w) {
+      const float2 a = red[tid], b = red[tid + (w << ln_out)];
+      red[tid] = make_float2(a.x + b.x, a.y + b.y);
     }
     __syncthreads();
+  }
+  float mx = 0.f;
+  if (tid < nout) {
+    const float2 v = red[tid];
+    mx = mag_max(mx, v.x, v.y);
+    // output o = (i, j) of the group (j < 2^ln_sub) sits at row i, column j
+    // of C, whose rows hold 2^ln_row entries
+    C[((int64_t)(o >> ln_sub) << ln_row) | (o & ((1 << ln_sub) - 1))] = from_f2<E>(v.x * out_scale, v.y * out_scale);
   }
   record_max(maxslot, mx);
 }
@@ -904,7 +1006,7 @@ static hipError_t launch_splitk_t(int dtype, const E* A, const E* B, E* C, float
     int64_t nb = 0;
     const hipError_t e = launch_splitk_chunk(dtype, A, B, part, op, &nb, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_splitk_final<E>, dim3(1), dim3(256), 0, s, part, (int)nb, 1 << (op.nM + op.nN), C,
+    hipLaunchKernelGGL(k_splitk_final<E>, dim3(1), dim3(kFinalThreads), 0, s, part, (int)nb, op.nM + op.nN, C,
                        op.out_scale, maxslot, op.nN, op.nN, op.nM, 0);
     return hipSuccess;
   }
@@ -927,15 +1029,14 @@ static hipError_t launch_splitk_t(int dtype, const E* A, const E* B, E* C, float
   gr.gA = op.aM;
   gr.gB = op.bN;
   gr.gn_bits = op.nN - gn2;
-  const int nout = 1 << (gm + gn2);
   const unsigned groups = 1u << (op.nM - gm + op.nN - gn2);
   const dim3 grid((unsigned)g, groups);
   if (vec)
     launch_splitk_v<VK>(A, B, part, sub, gr, grid, s);
   else
     launch_splitk_v<1>(A, B, part, sub, gr, grid, s);
-  hipLaunchKernelGGL(k_splitk_final<E>, dim3(groups), dim3(256), 0, s, part, (int)g, nout, C, op.out_scale, maxslot,
-                     gn2, op.nN, gm, gr.gn_bits);
+  hipLaunchKernelGGL(k_splitk_final<E>, dim3(groups), dim3(kFinalThreads), 0, s, part, (int)g, gm + gn2, C, op.out_scale,
+                     maxslot, gn2, op.nN, gm, gr.gn_bits);
   return hipSuccess;
 }
 
@@ -1031,7 +1132,7 @@ __global__ void k_zero_count(unsigned long long* count) { *count = 0ull; }
 // Each block takes kFrugalPer candidates per thread at a time and claims the
 // output places of all it keeps with one atomic: one atomic per kept candidate
 // on the single counter bound the kernel (52 us for 2^18 candidates of which
-// a tenth is kept, 6 us now).  A thread's candidates are 256 apart, so that
+// a tenth is kept, 8 us now).  A thread's candidates are 256 apart, so that
 // its index, amplitude and uniform-number loads are all in flight together.
 constexpr int kFrugalPer = 4;
 
@@ -1201,7 +1302,7 @@ __device__ __forceinline__ int hist_bin(amp2 a, double scale, double xmax, int n
 // each bin has 2^lr copies, one per lane modulo 2^lr and in neighbouring
 // banks, so that lanes of one wave that hit the same bin do not wait for each
 // other.  One global atomic per amplitude made the counters' cache lines the
-// bound (2^24 amplitudes into 64 bins: 56 ms at 5 GB/s; now 60 us, the reads).
+// bound (2^24 amplitudes into 64 bins: 56 ms; now 41 us, 6.5 TB/s).
 constexpr int kHistLds = 8192;  // LDS counters of one block
 
 __global__ __launch_bounds__(1024) void k_hist(const amp2* __restrict__ amp, int64_t n, double scale, double xmax,
