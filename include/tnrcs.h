@@ -261,7 +261,9 @@ int tn_plan_info(tn_plan_t p, tn_plan_stats* s);
 /* Writes the plan as JSON (host folds, device leaves, per-step kernels with
  * layouts and arena offsets, and per device step its extents nM nN nK, its
  * kernel class (1 GEMM, 2 gathered, 3 skewed, 4 split-K), its
- * relabelled layout key and whether the class tuner chose it) into buf (capacity cap bytes, NUL-terminated);
+ * relabelled layout key and whether the class tuner chose it; "small_net":
+ * whether slices run as one launch each from on-chip memory instead of those
+ * kernels) into buf (capacity cap bytes, NUL-terminated);
  * *needed receives the full length + 1.  buf may be NULL to query the size. */
 int tn_plan_json(tn_plan_t p, char* buf, int64_t cap, int64_t* needed);
 

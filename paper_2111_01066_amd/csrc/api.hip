@@ -97,6 +97,10 @@ struct tn_plan_s {
   float* d_maxslots = nullptr;
   float* d_outscales = nullptr;
   double2* d_kappa = nullptr;  // scaled storage: per sub-block rounding factors of the sliced leaves
+  // small networks (core.small): program and per-slice results
+  SmallArgs small;
+  char* d_small = nullptr;
+  int64_t small_slices = 0;  // slices per launch that the results have room for
   double* d_stage = nullptr;   // checked runs: one slice's bunch before it joins the sum
   int64_t bind_max = 0;
   hipStream_t cap_stream = nullptr;
@@ -245,6 +249,42 @@ static int upload_scales(tn_plan_s* p) {
   HIP_TRY(hipMemcpy(p->d_outscales, sc.data(), sc.size() * sizeof(float), hipMemcpyHostToDevice), "upload scales");
   HIP_TRY(hipMemcpy(p->d_maxslots, zero.data(), zero.size() * sizeof(float), hipMemcpyHostToDevice),
           "clear magnitude records");
+  return TN_OK;
+}
+
+// Device copy of a small network's program, and behind it room for the results
+// of up to 4096 slices per launch (16 MiB at most), in one allocation.
+static int upload_small(tn_plan_s* p) {
+  const PlanCore& P = p->core;
+  const SmallNet& S = P.small;
+  if (!S.ok) return TN_OK;
+  std::vector<SmallLeaf> leaves = S.leaves;
+  if (p->d_kappa)  // offsets assigned when the leaves were rounded
+    for (size_t i = 0, j = 0; i < leaves.size(); ++i)
+      if (leaves[i].n_sl > 0) leaves[i].kappa_off = P.binds[j++].kappa_off;
+  auto pad = [](size_t n) { return (n + 255) / 256 * 256; };
+  const size_t b_tabs = pad(S.tabs.size() * 2), b_ops = pad(S.ops.size() * sizeof(SmallOp)),
+               b_leaves = pad(leaves.size() * sizeof(SmallLeaf));
+  const int64_t n_amp = (int64_t)1 << P.accum.n_open;
+  p->small_slices = std::min<int64_t>({P.stats.n_slices, 4096, ((int64_t)1 << 21) / n_amp});
+  const int64_t ns = p->small_slices > 1 ? p->small_slices : 0;
+  const size_t b_factors = pad((size_t)ns * sizeof(double2)), b_roots = pad((size_t)(ns * n_amp) * sizeof(float2));
+  HIP_TRY(hipMalloc((void**)&p->d_small, b_tabs + b_ops + b_leaves + b_factors + b_roots), "alloc small network");
+  std::vector<char> h(b_tabs + b_ops + b_leaves, 0);
+  std::memcpy(h.data(), S.tabs.data(), S.tabs.size() * 2);
+  std::memcpy(h.data() + b_tabs, S.ops.data(), S.ops.size() * sizeof(SmallOp));
+  std::memcpy(h.data() + b_tabs + b_ops, leaves.data(), leaves.size() * sizeof(SmallLeaf));
+  HIP_TRY(hipMemcpy(p->d_small, h.data(), h.size(), hipMemcpyHostToDevice), "upload small network");
+  char* at = p->d_small;
+  p->small.tabs = reinterpret_cast<const uint16_t*>(at);
+  p->small.ops = reinterpret_cast<const SmallOp*>(at + b_tabs);
+  p->small.leaves = reinterpret_cast<const SmallLeaf*>(at + b_tabs + b_ops);
+  at += h.size();
+  if (ns > 0) {
+    p->small.factors = reinterpret_cast<double2*>(at);
+    p->small.roots = reinterpret_cast<float2*>(at + b_factors);
+  }
+  HIP_TRY(prepare_small(P.opts.dtype, S, P.n_slots), "small-network kernel");
   return TN_OK;
 }
 
@@ -562,6 +602,7 @@ static void release(tn_plan_s* p) {
   hipFree(p->d_maxslots);
   hipFree(p->d_outscales);
   if (p->d_kappa) hipFree(p->d_kappa);
+  if (p->d_small) hipFree(p->d_small);
   if (p->d_stage) hipFree(p->d_stage);
 }
 
@@ -698,6 +739,7 @@ int tn_plan(const tn_circuit* c, const int32_t* order_pairs, int32_t n_steps, co
   if (e != hipSuccess) return bail(hip_fail(e, "init control"));
   if (o.tune && (rc = tune_plan(p))) return bail(rc);
   if ((rc = calibrate(p))) return bail(rc);
+  if ((rc = upload_small(p))) return bail(rc);
   e = hipMemcpy(p->d_ctrl, &zero, sizeof(Ctrl), hipMemcpyHostToDevice);
   if (e != hipSuccess) return bail(hip_fail(e, "init control"));
   *out = p;
@@ -790,7 +832,7 @@ int tn_pair_run(tn_plan_t p, const void* A, const void* B, void* C, int64_t batc
 // (captured on first use) or enqueueing the kernels directly.
 // Captures the plan's per-slice graph once (plans with opts.use_graph).
 static int ensure_graph(tn_plan_s* p) {
-  if (!p->core.opts.use_graph || p->exec) return TN_OK;
+  if (!p->core.opts.use_graph || p->exec || p->core.small.ok) return TN_OK;
   if (!p->cap_stream) HIP_TRY(hipStreamCreateWithFlags(&p->cap_stream, hipStreamNonBlocking), "create capture stream");
   HIP_TRY(hipStreamBeginCapture(p->cap_stream, hipStreamCaptureModeThreadLocal), "begin capture");
   int rc = enqueue_slice(p, p->cap_stream);
@@ -819,6 +861,22 @@ static int run_slices(tn_plan_s* p, int64_t count, hipStream_t s) {
   return TN_OK;
 }
 
+// Slices [s0, s1) into amp: a small network's in one launch per small_slices
+// of them, else slice by slice from the control block's cursor.
+static int run_range(tn_plan_s* p, int64_t s0, int64_t s1, void* amp, hipStream_t s, bool clear_flags = false) {
+  const PlanCore& P = p->core;
+  if (!P.small.ok) {
+    HIP_TRY(launch_set_ctrl(p->d_ctrl, s0, amp, s, clear_flags), "control kernel");
+    return run_slices(p, s1 - s0, s);
+  }
+  if (clear_flags) HIP_TRY(launch_set_ctrl(p->d_ctrl, s0, amp, s, true), "control kernel");
+  for (int64_t b = s0; b < s1; b += p->small_slices)
+    HIP_TRY(launch_small(P.opts.dtype, p->d_leaves, P.small, p->small, P.accum, p->d_kappa, p->d_ctrl, p->d_outscales,
+                         P.n_slots, b, std::min<int64_t>(p->small_slices, s1 - b), (double*)amp, s),
+            "small-network kernel");
+  return TN_OK;
+}
+
 int tn_contract_slices(tn_plan_t p, int64_t s_begin, int64_t s_end, void* amp, void* stream) {
   if (!p) return fail(TN_E_ARG, "plan is NULL");
   if (p->core.pair_mode) return fail(TN_E_ARG, "pairwise plan: use tn_pair_run");
@@ -833,8 +891,7 @@ int tn_contract_slices(tn_plan_t p, int64_t s_begin, int64_t s_end, void* amp, v
   p->last_stream = s;
   p->ran = true;
   if (s_end == s_begin) return TN_OK;
-  HIP_TRY(launch_set_ctrl(p->d_ctrl, s_begin, amp, s), "control kernel");
-  return run_slices(p, s_end - s_begin, s);
+  return run_range(p, s_begin, s_end, amp, s);
 }
 
 int tn_contract_slices_checked(tn_plan_t p, int64_t s_begin, int64_t s_end, void* amp, void* stream,
@@ -864,8 +921,7 @@ int tn_contract_slices_checked(tn_plan_t p, int64_t s_begin, int64_t s_end, void
   for (int64_t sl = s_begin; sl < s_end && rc == TN_OK; ++sl) {
     for (int attempt = 0;; ++attempt) {
       HIP_TRY(hipMemsetAsync(p->d_stage, 0, (size_t)n_amp * 16, s), "clear staging bunch");
-      HIP_TRY(launch_set_ctrl(p->d_ctrl, sl, p->d_stage, s, true), "control kernel");
-      if ((rc = run_slices(p, 1, s))) break;
+      if ((rc = run_range(p, sl, sl + 1, p->d_stage, s, true))) break;
       HIP_TRY(hipStreamSynchronize(s), "stream synchronize");
       HIP_TRY(hipMemcpy(&c, p->d_ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost), "read control");
       const uint32_t range = c.flags & (TN_FLAG_OVERFLOW | TN_FLAG_UNDERFLOW);
@@ -1035,8 +1091,7 @@ int tn_batch_run(tn_batch_t b, void* stream) {
       const int i = b->lanes[k][j];
       tn_plan_s* p = b->plans[i];
       const int64_t s0 = b->ranges[2 * i], s1 = b->ranges[2 * i + 1];
-      HIP_TRY(launch_set_ctrl(p->d_ctrl, s0, b->amps[i], b->lane_streams[k]), "control kernel");
-      if (int rc = run_slices(p, s1 - s0, b->lane_streams[k])) return rc;
+      if (int rc = run_range(p, s0, s1, b->amps[i], b->lane_streams[k])) return rc;
     }
   for (size_t k = 0; k < b->lanes.size(); ++k) {
     HIP_TRY(hipEventRecord(b->join[k], b->lane_streams[k]), "batch join");

@@ -120,6 +120,33 @@ struct AccumDesc {
   double kappa0_re = 1.0, kappa0_im = 0.0;
 };
 
+// A network whose slice fits one workgroup's LDS (see small.hip): the same
+// device steps, on leaves and results held in LDS in their natural layouts.
+struct SmallOp {
+  int32_t nM = 0, nN = 0, nK = 0;
+  int32_t a = 0, b = 0, c = 0;  // LDS element offsets of the operands and the result
+  int32_t tab = 0;              // first of its offset tables: 2^nM A rows, 2^nN B columns, 2^nK A terms, B terms
+  int32_t slot = -1;            // output scale and magnitude record (scaled storage)
+};
+struct SmallLeaf {
+  int64_t src = 0;              // element offset in the leaves region
+  int64_t kappa_off = -1;       // scaled storage: its rounding factors (-1: none, unsliced)
+  int32_t dst = 0, n = 0;       // LDS element offset, entries of one slice
+  int32_t n_sl = 0;             // sliced wires: slice-id bits sbit[j] select offset bits pos[j]
+  int32_t sbit[8] = {}, pos[8] = {};
+};
+struct SmallNet {
+  bool ok = false;
+  std::vector<SmallOp> ops;
+  std::vector<SmallLeaf> leaves;
+  std::vector<uint16_t> tabs;
+  int32_t elems = 0;             // LDS elements of all tensors
+  int32_t root = 0, root_tab = 0;  // the final tensor; its 2^n_open offsets in amplitude order
+};
+constexpr int kSmallMaxRank = 14;           // tensors and amplitude buffers of at most 2^14 entries
+constexpr int kSmallLdsBytes = 144 * 1024;  // of a CU's 160 KB
+constexpr int kSmallMaxOps = 64;
+
 struct HostTensor {
   std::vector<int> wires;  // most significant first
   std::vector<std::complex<double>> data;
@@ -156,6 +183,7 @@ struct PlanCore {
   std::vector<int> root_layout;  // layout of the final tensor (wires, most significant first)
   int32_t n_slots = 0;  // producing ops with a magnitude record (scaled storage)
   tn_plan_stats stats{};
+  SmallNet small;
   std::string json;
 
   // kernel class per device step: the planner's rule unless the autotuner

@@ -71,6 +71,22 @@ bool splitk_chunk_aligned(const IndexOp& op);
 // sliced_factors, by the per-slice factor that the bind kernel left in ctrl.
 hipError_t launch_accum(int dtype, const void* root, const AccumDesc& d, Ctrl* ctrl, float* maxslots,
                         const float* out_scales, int n_slots, bool sliced_factors, hipStream_t s);
+// Slices s_begin .. s_begin + count of a small network (PlanCore::small), one
+// workgroup per slice; amp += their sum in slice order.  roots (count x
+// 2^n_open float2) and factors (count double2) are workspace, unused for
+// count 1; ops, leaves, tabs: device copies of the SmallNet's.
+struct SmallArgs {
+  const SmallOp* ops = nullptr;
+  const SmallLeaf* leaves = nullptr;
+  const uint16_t* tabs = nullptr;
+  float2* roots = nullptr;
+  double2* factors = nullptr;
+};
+hipError_t launch_small(int dtype, const void* leaf_data, const SmallNet& net, const SmallArgs& a, const AccumDesc& d,
+                        const double2* kappa, Ctrl* ctrl, const float* out_scales, int n_slots, int64_t s_begin,
+                        int64_t count, double* amp, hipStream_t s);
+// Raises the kernel's LDS limit to what the network needs (once per plan).
+hipError_t prepare_small(int dtype, const SmallNet& net, int n_slots);
 hipError_t launch_frugal(const double* amp, int64_t n, const int64_t* idx, int64_t n_cand, const double* u,
                          double scale, double m, int64_t* out, unsigned long long* count, hipStream_t s);
 hipError_t launch_norm2(const double* amp, int64_t n, double* out, hipStream_t s);

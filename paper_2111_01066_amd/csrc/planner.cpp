@@ -307,7 +307,7 @@ void make_json(PlanCore& P) {
     js << (i ? "," : "") << "{\"t\":" << st.t << ",\"nM\":" << st.nM << ",\"nN\":" << st.nN << ",\"nK\":" << st.nK
        << ",\"cls\":" << st.cls << ",\"key\":\"" << st.key << "\",\"tuned\":" << (P.class_override.count(st.t) ? "true" : "false") << "}";
   }
-  js << "],\"accum\":{\"n_open\":" << P.accum.n_open << ",\"root\":";
+  js << "],\"small_net\":" << (P.small.ok ? "true" : "false") << ",\"accum\":{\"n_open\":" << P.accum.n_open << ",\"root\":";
   json_ref(js, P.accum.root);
   js << ",\"y2root\":";
   json_runs(js, P.accum.y2root);
@@ -380,6 +380,98 @@ static PlanCore::StepInfo step_info(int t, const std::vector<int>& La, const std
   relabel(Lb, st.lb);
   relabel(Lc, st.lc);
   return st;
+}
+
+// Offsets, in a tensor of the given layout, of every value of the bits `wires`
+// (most significant first).
+static void push_offsets(const std::vector<int>& layout, const std::vector<int>& wires, std::vector<uint16_t>& out) {
+  const int r = (int)wires.size();
+  for (int v = 0; v < 1 << r; ++v) {
+    int o = 0;
+    for (int i = 0; i < r; ++i)
+      if (v >> i & 1) o |= 1 << pos_in(layout, wires[r - 1 - i]);
+    out.push_back((uint16_t)o);
+  }
+}
+
+// One step of the plan as the small-network form needs it.
+struct SmallStep {
+  int ia, ib, ic;                 // SSA ids of the operands and the result
+  std::vector<int> La, Lb, m, n, k;  // operand layouts; free wires of A and B, contracted wires
+};
+
+// The small-network form of the plan (small.hip): every tensor of a slice in
+// one workgroup's LDS.  Rule: all tensors of rank kSmallMaxRank or less,
+// leaves, results and tables within kSmallLdsBytes, and a time below that of
+// the plan's own launches for a single slice.  Measured: the one launch takes
+// 56 us per 2^20 multiply-adds in 4 x 4 output blocks, twice that in 2 x 2
+// blocks and four times with one output per lane, against 7 us for each
+// launch of the plan (2^18.6 multiply-adds in 3 launches: 39 against 46 us;
+// 2^18 in 4: 33 against 56).  Calls over many slices gain far more, since
+// they run side by side, but the form has to be the plan's for every range:
+// splitting a range must give the same sum.
+static void build_small(PlanCore& P, const std::vector<SmallStep>& steps, const std::vector<std::vector<int>>& lay) {
+  SmallNet& S = P.small;
+  S = SmallNet{};
+  if (P.pair_mode || steps.empty() || steps.size() > kSmallMaxOps || (int)P.open_wires.size() > kSmallMaxRank) return;
+  double cost = 0;
+  for (const SmallStep& st : steps) {
+    const int nM = (int)st.m.size(), nN = (int)st.n.size(), nK = (int)st.k.size();
+    if (nM + nK > kSmallMaxRank || nN + nK > kSmallMaxRank || nM + nN > kSmallMaxRank) return;
+    const bool wide = nM + nN >= 12 && nM >= 2 && nN >= 2, block = nM + nN >= 10 && nM >= 1 && nN >= 1;
+    cost += std::ldexp(wide ? 1.0 : block ? 2.0 : 4.0, nM + nN + nK);
+  }
+  if (cost > std::ldexp((double)(P.ops.size() + 1 + (P.binds.empty() ? 0 : 1)), 17)) return;
+  // LDS placement: leaves from the start to their consumer, results from
+  // their step to theirs
+  std::vector<Buf> bufs;
+  std::map<int, int> buf_of;
+  for (const DevLeaf& d : P.dev_leaves) {
+    buf_of[d.ssa] = (int)bufs.size();
+    bufs.push_back({(int64_t)(d.data.size() >> d.n_sliced), 0, 0, -1, (int)bufs.size()});
+  }
+  for (int t = 0; t < (int)steps.size(); ++t) {
+    for (int x : {steps[t].ia, steps[t].ib}) bufs[buf_of[x]].t1 = t;
+    buf_of[steps[t].ic] = (int)bufs.size();
+    bufs.push_back({(int64_t)1 << (steps[t].m.size() + steps[t].n.size()), t, t, -1, (int)bufs.size()});
+  }
+  S.elems = (int32_t)place_buffers(bufs);
+  int slot = 0;
+  for (const SmallStep& st : steps) {
+    SmallOp op;
+    op.nM = (int)st.m.size();
+    op.nN = (int)st.n.size();
+    op.nK = (int)st.k.size();
+    op.a = (int32_t)bufs[buf_of[st.ia]].off;
+    op.b = (int32_t)bufs[buf_of[st.ib]].off;
+    op.c = (int32_t)bufs[buf_of[st.ic]].off;
+    op.tab = (int32_t)S.tabs.size();
+    if (P.opts.dtype != TN_DTYPE_C64) op.slot = slot++;  // one magnitude record per step, in order
+    push_offsets(st.La, st.m, S.tabs);
+    push_offsets(st.Lb, st.n, S.tabs);
+    push_offsets(st.La, st.k, S.tabs);
+    push_offsets(st.Lb, st.k, S.tabs);
+    S.ops.push_back(op);
+  }
+  S.root = S.ops.back().c;
+  S.root_tab = (int32_t)S.tabs.size();
+  push_offsets(lay[steps.back().ic], P.open_wires, S.tabs);
+  while (S.tabs.size() % 8) S.tabs.push_back(0);
+  for (const DevLeaf& d : P.dev_leaves) {
+    SmallLeaf l;
+    l.src = d.stored_off;
+    l.dst = (int32_t)bufs[buf_of[d.ssa]].off;
+    l.n = (int32_t)(d.data.size() >> d.n_sliced);
+    l.n_sl = d.n_sliced;
+    for (int i = 0; i < d.n_sliced; ++i) {
+      l.sbit[i] = d.slice_bit[i];
+      l.pos[i] = (int)d.layout.size() - 1 - i;
+    }
+    S.leaves.push_back(l);
+  }
+  const int64_t lds = (int64_t)S.elems * elem_bytes_plan(P) + (int64_t)S.tabs.size() * 2 +
+                      (int64_t)(S.ops.size() * sizeof(SmallOp) + steps.size() * 4);
+  S.ok = lds <= kSmallLdsBytes;
 }
 
 int build_plan(PlanCore& P, std::string& err) {
@@ -574,6 +666,7 @@ int build_plan(PlanCore& P, std::string& err) {
   P.stats.flops_per_slice = P.stats.bytes_per_slice = P.stats.moved_per_slice = 0;
   P.stats.n_dense = P.stats.n_skinny = P.stats.n_generic = P.stats.n_permute = 0;
   std::vector<int> step_time(S, -1);
+  std::vector<SmallStep> small_steps;
   for (int t = 0; t < S; ++t) {
     if (P.on_host[L + t]) continue;
     step_time[t] = dstep;
@@ -599,6 +692,7 @@ int build_plan(PlanCore& P, std::string& err) {
     std::vector<int> Lc = MA;
     Lc.insert(Lc.end(), NB.begin(), NB.end());
     lay[L + t] = Lc;
+    if (!P.pair_mode) small_steps.push_back({ia, ib, L + t, La, Lb, MA, NB, K});
     // result buffer
     Buf cb{(int64_t)1 << rcn, dstep, dstep, -1, (int)bufs.size()};
     int cbuf = (int)bufs.size();
@@ -888,6 +982,7 @@ int build_plan(PlanCore& P, std::string& err) {
     else
       P.accum.root = TRef{kArena, bufs[buf_of_ssa[root]].off};
   }
+  build_small(P, small_steps, lay);
   if (P.opts.max_log2 > 0 && max_log2 > P.opts.max_log2) {
     err = "a per-slice tensor has 2^" + std::to_string(max_log2) + " entries, above the bound 2^" +
           std::to_string(P.opts.max_log2);
