@@ -59,6 +59,28 @@ __device__ __forceinline__ void skew_split(const SkewMap& mp, int e, uint64_t& o
   }
 }
 
+// 16-bit storage, 16-byte loads: the four entries of a load differ in the
+// chunk's two lowest address bits.  The planar LDS rows hold k contiguously,
+// so a thread keeps all four entries of k bits 0 and 1 of its rows and stores
+// them together: the k bits that the load does not cover are the ones that
+// tell the thread's loads apart.  How they sit: kQuadKK: the load covers k0,
+// k1; kQuadKR: k0, then a row bit; kQuadRK: a row bit, then k0; kQuadRR: two
+// row bits.
+enum QuadMode : int { kQuadKK = 0, kQuadKR = 1, kQuadRK = 2, kQuadRR = 3 };
+
+// Host: the mode of a chunk map (entries sorted by position), whose entries
+// are reordered so that the last ones tell a thread's 2^lj loads apart: k1
+// (kQuadKR, kQuadRK), or k0 and, with lj = 2, k1 (kQuadRR; then k0 before k1).
+// -1: the two lowest positions are not in the chunk, or hold k bits other
+// than these.
+int quad_mode(SkewMap* mp, int lj);
+
+// Four 16-bit pairs (re, im) as two words of re and two of im.
+__device__ __forceinline__ void quad_split(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, uint2& re, uint2& im) {
+  re = make_uint2(__builtin_amdgcn_perm(w1, w0, 0x05040100u), __builtin_amdgcn_perm(w3, w2, 0x05040100u));
+  im = make_uint2(__builtin_amdgcn_perm(w1, w0, 0x07060302u), __builtin_amdgcn_perm(w3, w2, 0x07060302u));
+}
+
 // Host: the chunk map of rows 0..127 (op.aM bits 0..6) and k bits
 // 0..kcb-1 (op.aK), with the bank swizzle for stores that cover chunk bits
 // lv .. lv+4.  False when a bit has no position.

@@ -374,11 +374,11 @@ __global__ __launch_bounds__(512, 1) void k_hgemm_pp(const E* __restrict__ A, co
 
 // A read in place (4M, 128x128 tiles, stages of 32 k, two waves per SIMD):
 // the stage's 128 x 32 A entries are gathered through the chunk map in A's
-// address order, four consecutive addresses per 16-byte load.  Those four
-// entries differ in A's two lowest index bits, which are the lowest row or
-// k bits; MODE says which (0: k0 k1, four k of one row; 1: k0 then row 0;
-// 2: row 0 then k0; 3: row 0 row 1, four rows at one k), and so how they are
-// deinterleaved into the planar [row][k] LDS rows.  The stage's K offset
+// address order, four consecutive addresses per 16-byte load, and stored to
+// the planar [row][k] LDS rows four k at a time (MODE: QuadMode).  Where the
+// load covers row bits, storing its entries one by one (2-byte LDS stores, 32
+// per thread and stage) held the kernel to 730 complex TFLOP/s on the rank-27 x
+// rank-25 pair, 1010 with eight 8-byte stores.  The stage's K offset
 // moves by a carrying add restricted to A's K bits above 4 (in increasing
 // positions).  B is [N][K] and C is [M][N], as in k_hgemm.
 struct GatherAH {
@@ -409,7 +409,8 @@ __global__ __launch_bounds__(256, 2) void k_hgemm_ga(const E* __restrict__ A, co
 #pragma unroll
       for (int j = 0; j < WTN; ++j) acc[p][i][j] = floatx16{};
   // this thread's four loads of a stage: offset of the first entry from the
-  // stage's first entry, and the LDS index (row * LDK + k) of that entry
+  // stage's first entry, and the LDS index (row * LDK + k) of that entry;
+  // LDS offset of the row bits that a load covers
   uint32_t eoff[4];
   int lidx[4];
 #pragma unroll
@@ -420,6 +421,8 @@ __global__ __launch_bounds__(256, 2) void k_hgemm_ga(const E* __restrict__ A, co
     eoff[j] = (uint32_t)off;
     lidx[j] = m * LDK + k;
   }
+  const int row0 = (1 << (MODE == kQuadKR ? g.mp.mb[1] : MODE == kQuadKK ? 0 : g.mp.mb[0])) * LDK;
+  const int row1 = MODE == kQuadRR ? (1 << g.mp.mb[1]) * LDK : 0;
   const uint64_t abase = dep_u<12>((uint64_t)bm, g.aM);
   uint64_t kofs = 0;
   const int brow = tid / 2, bk = (tid % 2) * 16;
@@ -433,32 +436,39 @@ __global__ __launch_bounds__(256, 2) void k_hgemm_ga(const E* __restrict__ A, co
   auto store_a = [&](H (*S)[BM][LDK]) {
     H* re = &S[0][0][0];
     H* im = &S[1][0][0];
+    uint32_t w[4][4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const uint32_t w[4] = {ra[j].x, ra[j].y, ra[j].z, ra[j].w};
-      const int i0 = lidx[j];
-      if constexpr (MODE == 0) {  // k, k+1, k+2, k+3 of one row
-        *reinterpret_cast<uint2*>(re + i0) = make_uint2(__builtin_amdgcn_perm(w[1], w[0], 0x05040100u),
-                                                        __builtin_amdgcn_perm(w[3], w[2], 0x05040100u));
-        *reinterpret_cast<uint2*>(im + i0) = make_uint2(__builtin_amdgcn_perm(w[1], w[0], 0x07060302u),
-                                                        __builtin_amdgcn_perm(w[3], w[2], 0x07060302u));
-      } else if constexpr (MODE == 1) {  // (m, k), (m, k+1), (m+1, k), (m+1, k+1)
-        *reinterpret_cast<uint32_t*>(re + i0) = __builtin_amdgcn_perm(w[1], w[0], 0x05040100u);
-        *reinterpret_cast<uint32_t*>(im + i0) = __builtin_amdgcn_perm(w[1], w[0], 0x07060302u);
-        *reinterpret_cast<uint32_t*>(re + i0 + LDK) = __builtin_amdgcn_perm(w[3], w[2], 0x05040100u);
-        *reinterpret_cast<uint32_t*>(im + i0 + LDK) = __builtin_amdgcn_perm(w[3], w[2], 0x07060302u);
-      } else if constexpr (MODE == 2) {  // (m, k), (m+1, k), (m, k+1), (m+1, k+1)
-        *reinterpret_cast<uint32_t*>(re + i0) = __builtin_amdgcn_perm(w[2], w[0], 0x05040100u);
-        *reinterpret_cast<uint32_t*>(im + i0) = __builtin_amdgcn_perm(w[2], w[0], 0x07060302u);
-        *reinterpret_cast<uint32_t*>(re + i0 + LDK) = __builtin_amdgcn_perm(w[3], w[1], 0x05040100u);
-        *reinterpret_cast<uint32_t*>(im + i0 + LDK) = __builtin_amdgcn_perm(w[3], w[1], 0x07060302u);
-      } else {  // rows m .. m+3 at one k
+      w[j][0] = ra[j].x;
+      w[j][1] = ra[j].y;
+      w[j][2] = ra[j].z;
+      w[j][3] = ra[j].w;
+    }
+    auto put = [&](int at, uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3) {
+      uint2 r, i;
+      quad_split(w0, w1, w2, w3, r, i);
+      *reinterpret_cast<uint2*>(re + at) = r;
+      *reinterpret_cast<uint2*>(im + at) = i;
+    };
+    if constexpr (MODE == kQuadKK) {  // each load: four k of one row
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          re[i0 + q * LDK] = __builtin_bit_cast(H, (uint16_t)(w[q] & 0xFFFFu));
-          im[i0 + q * LDK] = __builtin_bit_cast(H, (uint16_t)(w[q] >> 16));
-        }
+      for (int j = 0; j < 4; ++j) put(lidx[j], w[j][0], w[j][1], w[j][2], w[j][3]);
+    } else if constexpr (MODE == kQuadKR) {  // loads j, j + 2 (k1 = 0, 1): (k0, row)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        put(lidx[j], w[j][0], w[j][1], w[j + 2][0], w[j + 2][1]);
+        put(lidx[j] + row0, w[j][2], w[j][3], w[j + 2][2], w[j + 2][3]);
       }
+    } else if constexpr (MODE == kQuadRK) {  // loads j, j + 2 (k1 = 0, 1): (row, k0)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        put(lidx[j], w[j][0], w[j][2], w[j + 2][0], w[j + 2][2]);
+        put(lidx[j] + row0, w[j][1], w[j][3], w[j + 2][1], w[j + 2][3]);
+      }
+    } else {  // loads 0 .. 3: k0, k1; their entries: two row bits
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        put(lidx[0] + (v & 1) * row0 + (v >> 1) * row1, w[0][v], w[1][v], w[2][v], w[3][v]);
     }
   };
   auto load_b = [&](int64_t k0) {
@@ -563,14 +573,13 @@ static hipError_t hgemm_ga_t(const E* A, const E* B, E* C, const IndexOp& idx, f
   g.aM = idx.aM;
   g.maskK = dep_host_h((uint64_t)(K - 1) & ~(uint64_t)31, idx.aK);
   g.incK = K > 32 ? dep_host_h(32, idx.aK) : 0;
-  // the two lowest chunk bits are A's positions 0 and 1
-  if (g.mp.pos[0] != 0 || g.mp.pos[1] != 1) return hipErrorInvalidValue;
-  const bool k0 = g.mp.kb[0] == 0, k1 = g.mp.kb[1] == 1, m0 = g.mp.mb[0] == 0, m1 = g.mp.mb[1] == 1;
-  if (k0 && k1) hgemm_ga_launch<0, H, E>(A, B, C, M, N, K, scale, maxslot, g, s);
-  else if (k0 && g.mp.mb[1] == 0) hgemm_ga_launch<1, H, E>(A, B, C, M, N, K, scale, maxslot, g, s);
-  else if (m0 && g.mp.kb[1] == 0) hgemm_ga_launch<2, H, E>(A, B, C, M, N, K, scale, maxslot, g, s);
-  else if (m0 && m1) hgemm_ga_launch<3, H, E>(A, B, C, M, N, K, scale, maxslot, g, s);
-  else return hipErrorInvalidValue;
+  switch (quad_mode(&g.mp, 2)) {
+    case kQuadKK: hgemm_ga_launch<kQuadKK, H, E>(A, B, C, M, N, K, scale, maxslot, g, s); break;
+    case kQuadKR: hgemm_ga_launch<kQuadKR, H, E>(A, B, C, M, N, K, scale, maxslot, g, s); break;
+    case kQuadRK: hgemm_ga_launch<kQuadRK, H, E>(A, B, C, M, N, K, scale, maxslot, g, s); break;
+    case kQuadRR: hgemm_ga_launch<kQuadRR, H, E>(A, B, C, M, N, K, scale, maxslot, g, s); break;
+    default: return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 

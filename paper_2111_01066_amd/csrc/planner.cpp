@@ -121,6 +121,33 @@ HostTensor host_contract(const HostTensor& X, const HostTensor& Y, const std::ve
   return Z;
 }
 
+// K order for the 16-bit kernels that read A in place in chunks of 2^kcb k
+// (its lowest contracted bits), four consecutive entries per load: K (most
+// significant first, in A's order) with the chunk's bits reordered so that k
+// bits 0 and 1 are the ones a thread holds together (gather.h, QuadMode).
+// Those that the load does not cover are the chunk's highest, so that
+// neighbouring threads still read neighbouring addresses.
+std::vector<int> quad_order(const std::vector<int>& La, const std::vector<int>& K, int kcb) {
+  const int n = (int)K.size();
+  if (n < kcb) return K;
+  std::vector<int> low;  // the chunk's bits, lowest position first
+  for (int i = 0; i < kcb; ++i) low.push_back(K[n - 1 - i]);
+  const int in_load = (int)std::count_if(low.begin(), low.end(), [&](int w) { return pos_in(La, w) < 2; });
+  if (in_load < 2) {
+    const int last = low.back();
+    low.pop_back();
+    low.insert(low.begin() + in_load, last);
+    if (in_load == 0) {  // two row bits in the load: the two highest
+      const int next = low.back();
+      low.pop_back();
+      low.insert(low.begin() + 1, next);
+    }
+  }
+  std::vector<int> out(K.begin(), K.end() - kcb);
+  out.insert(out.end(), low.rbegin(), low.rend());
+  return out;
+}
+
 struct Buf {
   int64_t elems;
   int t0, t1;
@@ -755,12 +782,13 @@ int build_plan(PlanCore& P, std::string& err) {
           std::vector<int> p;
           for (int i = 0; i < nM; ++i) p.push_back(pos_in(La, MA[nM - 1 - i]));
           bool ok = make_runs(p, &gidx.aM);
+          const std::vector<int> Kg = half ? quad_order(La, K, 5) : K;
           p.clear();
-          for (int i = 0; i < nK; ++i) p.push_back(pos_in(La, K[nK - 1 - i]));
+          for (int i = 0; i < nK; ++i) p.push_back(pos_in(La, Kg[nK - 1 - i]));
           ok = ok && make_runs(p, &gidx.aK);
           if (ok && gemm_gather_ok(gidx)) {
             gather = true;
-            Kord = K;
+            Kord = Kg;
           }
         }
       }
@@ -870,6 +898,7 @@ int build_plan(PlanCore& P, std::string& err) {
       // (of 2^12 entries or more) is first permuted to [free wires, K]
       int tmp[2] = {-1, -1};
       std::vector<int> lay2[2] = {La, Lb};
+      if (half && cls == kOpSkew && nK >= 4) K = quad_order(La, K, 4);
       // the matrix-core skewed kernel with a long sum stages B chunk by
       // chunk: a B whose low k bits are scattered is permuted first too
       // (B only; A is read in place)

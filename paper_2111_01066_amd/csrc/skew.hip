@@ -450,7 +450,57 @@ struct SkewHalf<cbf16> {
   }
 };
 
-template <int NT, int VEC, int NCH, int PD, typename E>
+// A chunk's entries of this thread (two 16-byte loads, or VEC = 1: eight
+// 4-byte ones) to the planar rows at `s` (re plane, im plane 128 rows
+// further), by QuadMode: the loads of kQuadKR and kQuadRK differ in k1, so
+// they hold four k of two rows; those of kQuadRR differ in k0: two k of four
+// rows.  (Sixteen 2-byte stores per thread and chunk instead of four to eight
+// wider ones held the K = 512 step of 2^20 rows to 2.0 TB/s; 3.4 now.)
+template <int VEC, int MODE, int LPT, typename E, typename H>
+__device__ __forceinline__ void skew_store_half(H* s, const E (&v)[LPT][VEC], const int (&eidx)[LPT][VEC], int row0,
+                                                int row1) {
+  constexpr int IM = kSkewPM * kSkewHS;
+  if constexpr (VEC == 1) {
+#pragma unroll
+    for (int j = 0; j < LPT; ++j) {
+      s[eidx[j][0]] = v[j][0].re;
+      s[IM + eidx[j][0]] = v[j][0].im;
+    }
+  } else {
+    static_assert(LPT == 2 && VEC == 4, "two loads of four entries");
+    uint32_t w[2][4];
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) w[j][u] = __builtin_bit_cast(uint32_t, v[j][u]);
+    auto put4 = [&](int at, uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3) {
+      uint2 r, i;
+      quad_split(w0, w1, w2, w3, r, i);
+      *reinterpret_cast<uint2*>(s + at) = r;
+      *reinterpret_cast<uint2*>(s + IM + at) = i;
+    };
+    const int e0 = eidx[0][0], e1 = eidx[1][0];
+    if constexpr (MODE == kQuadKK) {
+      put4(e0, w[0][0], w[0][1], w[0][2], w[0][3]);
+      put4(e1, w[1][0], w[1][1], w[1][2], w[1][3]);
+    } else if constexpr (MODE == kQuadKR) {
+      put4(e0, w[0][0], w[0][1], w[1][0], w[1][1]);
+      put4(e0 + row0, w[0][2], w[0][3], w[1][2], w[1][3]);
+    } else if constexpr (MODE == kQuadRK) {
+      put4(e0, w[0][0], w[0][2], w[1][0], w[1][2]);
+      put4(e0 + row0, w[0][1], w[0][3], w[1][1], w[1][3]);
+    } else {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int at = e0 + (u & 1) * row0 + (u >> 1) * row1;
+        *reinterpret_cast<uint32_t*>(s + at) = __builtin_amdgcn_perm(w[1][u], w[0][u], 0x05040100u);
+        *reinterpret_cast<uint32_t*>(s + IM + at) = __builtin_amdgcn_perm(w[1][u], w[0][u], 0x07060302u);
+      }
+    }
+  }
+}
+
+template <int NT, int VEC, int MODE, int NCH, int PD, typename E>
 __global__ __launch_bounds__(256, 2) void k_skew_ph(const E* __restrict__ A, const E* __restrict__ B,
                                                    E* __restrict__ C, const IndexOp op, const SkewMap mp,
                                                    float* maxslot) {
@@ -466,6 +516,9 @@ __global__ __launch_bounds__(256, 2) void k_skew_ph(const E* __restrict__ A, con
   uint64_t* bn = reinterpret_cast<uint64_t*>(Bs + 2 * NP * KS);  // [64]
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = lane & 31, kh = lane >> 5;
+  // LDS offsets of the row bits that a 16-byte load covers
+  const int row0 = (1 << (MODE == kQuadKR ? mp.mb[1] : MODE == kQuadKK ? 0 : mp.mb[0])) * kSkewHS;
+  const int row1 = MODE == kQuadRR ? (1 << mp.mb[1]) * kSkewHS : 0;
   if (tid < 64) bn[tid] = tid < N ? dep((uint64_t)tid, op.bN) : 0;
   uint64_t kA0[NCH];
 #pragma unroll
@@ -534,13 +587,7 @@ __global__ __launch_bounds__(256, 2) void k_skew_ph(const E* __restrict__ A, con
 #pragma unroll
       for (int ch = 0; ch < NCH; ++ch) {
         __syncthreads();
-#pragma unroll
-        for (int j = 0; j < LPT; ++j)
-#pragma unroll
-          for (int u = 0; u < VEC; ++u) {
-            As[eidx[j][u]] = v[d][ch][j][u].re;
-            As[kSkewPM * kSkewHS + eidx[j][u]] = v[d][ch][j][u].im;
-          }
+        skew_store_half<VEC, MODE>(As, v[d][ch], eidx, row0, row1);
         load_chunk(v[d][ch], ch);
         __syncthreads();
         const V ar = *reinterpret_cast<const V*>(As + arow);
@@ -588,7 +635,7 @@ static size_t skew_ph_lds(int K, int np) { return 2 * kSkewPM * kSkewHS * 2 + 2 
 // pass the loads repeat the last pass's chunks (read, never used).
 constexpr int kSkewBS = 24;  // LDS row stride of a staged B chunk (entries)
 
-template <int NT, int VEC, typename E>
+template <int NT, int VEC, int MODE, typename E>
 __global__ __launch_bounds__(256, 2) void k_skew_phc(const E* __restrict__ A, const E* __restrict__ B,
                                                     E* __restrict__ C, const IndexOp op, const SkewMap mp,
                                                     float* maxslot) {
@@ -605,6 +652,9 @@ __global__ __launch_bounds__(256, 2) void k_skew_phc(const E* __restrict__ A, co
   const int nch = 1 << (op.nK - 4);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = lane & 31, kh = lane >> 5;
+  // LDS offsets of the row bits that a 16-byte load covers
+  const int row0 = (1 << (MODE == kQuadKR ? mp.mb[1] : MODE == kQuadKK ? 0 : mp.mb[0])) * kSkewHS;
+  const int row1 = MODE == kQuadRR ? (1 << mp.mb[1]) * kSkewHS : 0;
   // prefix tables: chunk ch -> ch + 1 flips the chunk-index bits 0 .. ctz(ch + 1)
   if (tid < op.nK - 4) {
     uint64_t xa = 0, xb = 0;
@@ -628,16 +678,13 @@ __global__ __launch_bounds__(256, 2) void k_skew_phc(const E* __restrict__ A, co
       eidx[j][u] = m * kSkewHS + k;
     }
   }
+  // B: NBT consecutive k of row bn per thread
+  const int bn = tid / (KC / NBT), bk = tid % (KC / NBT) * NBT, bidx = bn * kSkewBS + bk;
+  const bool bval = bn < N;
   uint64_t boff[NBT];
-  int bidx[NBT];
-  bool bval[NBT];
 #pragma unroll
-  for (int r = 0; r < NBT; ++r) {
-    const int i = r * 256 + tid, n = i / KC, k = i % KC;
-    bval[r] = n < N;
-    boff[r] = bval[r] ? (dep((uint64_t)n, op.bN) | dep((uint64_t)k, op.bK)) : 0;
-    bidx[r] = n * kSkewBS + k;
-  }
+  for (int r = 0; r < NBT; ++r)
+    boff[r] = bval ? (dep((uint64_t)bn, op.bN) | dep((uint64_t)(bk + r), op.bK)) : 0;
   const int64_t passes = ((int64_t)1 << op.nM) / kSkewPM;
   const int64_t my_passes = passes > (int64_t)blockIdx.x ? (passes - blockIdx.x + gridDim.x - 1) / gridDim.x : 0;
   const uint64_t mask_m = dep(((uint64_t)1 << op.nM) - kSkewPM, op.aM);
@@ -688,18 +735,21 @@ __global__ __launch_bounds__(256, 2) void k_skew_phc(const E* __restrict__ A, co
 #pragma unroll
       for (int d = 0; d < 2; ++d) {
         __syncthreads();  // the previous chunk's products have read As and Bs
+        skew_store_half<VEC, MODE>(As, v[d], eidx, row0, row1);
+        // this thread's NBT consecutive k of one row of B
+        {
+          uint32_t x[NBT];
 #pragma unroll
-        for (int j = 0; j < LPT; ++j)
-#pragma unroll
-          for (int u = 0; u < VEC; ++u) {
-            As[eidx[j][u]] = v[d][j][u].re;
-            As[kSkewPM * kSkewHS + eidx[j][u]] = v[d][j][u].im;
+          for (int r = 0; r < NBT; ++r) x[r] = bval ? __builtin_bit_cast(uint32_t, w[d][r]) : 0u;
+          if constexpr (NBT == 4) {
+            uint2 re, im;
+            quad_split(x[0], x[1], x[2], x[3], re, im);
+            *reinterpret_cast<uint2*>(Bs + bidx) = re;
+            *reinterpret_cast<uint2*>(Bs + NP * kSkewBS + bidx) = im;
+          } else {
+            *reinterpret_cast<uint32_t*>(Bs + bidx) = __builtin_amdgcn_perm(x[1], x[0], 0x05040100u);
+            *reinterpret_cast<uint32_t*>(Bs + NP * kSkewBS + bidx) = __builtin_amdgcn_perm(x[1], x[0], 0x07060302u);
           }
-#pragma unroll
-        for (int r = 0; r < NBT; ++r) {
-          const E x = bval[r] ? w[d][r] : E{};
-          Bs[bidx[r]] = x.re;
-          Bs[NP * kSkewBS + bidx[r]] = x.im;
         }
         prefetch(d);  // two chunks ahead
         __syncthreads();
@@ -883,63 +933,87 @@ static hipError_t launch_skew_t(const E* A, const E* B, E* C, const IndexOp& op,
   return launch_skew_kc<NT, 1, E>(A, B, C, op, mp, maxslot, s);
 }
 
-template <int NT, int VEC, int NCH, typename E>
+int quad_mode(SkewMap* mp, int lj) {
+  if (mp->v < 2 || mp->pos[0] != 0 || mp->pos[1] != 1) return -1;
+  const int a = mp->kb[0], b = mp->kb[1];  // -1: a row bit
+  if (a == 0 && b == 1) return kQuadKK;
+  if ((a >= 0 && (a != 0 || b >= 0)) || (b >= 0 && b != 0)) return -1;
+  const int mode = a == 0 ? kQuadKR : b == 0 ? kQuadRK : kQuadRR;
+  // moves the entry of k bit `kb` to the end of the map
+  auto to_end = [&](int kb) {
+    for (int i = 2; i < mp->v; ++i) {
+      if (mp->kb[i] != kb) continue;
+      const int8_t p = mp->pos[i], m = mp->mb[i], k = mp->kb[i];
+      for (int t = i; t + 1 < mp->v; ++t) {
+        mp->pos[t] = mp->pos[t + 1];
+        mp->mb[t] = mp->mb[t + 1];
+        mp->kb[t] = mp->kb[t + 1];
+      }
+      mp->pos[mp->v - 1] = p;
+      mp->mb[mp->v - 1] = m;
+      mp->kb[mp->v - 1] = k;
+      return true;
+    }
+    return false;
+  };
+  bool ok = true;
+  if (mode == kQuadRR) {
+    ok = to_end(0);
+    if (lj == 2) ok = ok && to_end(1);
+  } else {
+    ok = to_end(1);
+  }
+  return ok ? mode : -1;
+}
+
+template <int NT, int VEC, int MODE, int NCH, typename E>
 static hipError_t launch_skew_half(const E* A, const E* B, E* C, const IndexOp& op, const SkewMap& mp,
                                    float* maxslot, hipStream_t s) {
   constexpr int PD = NCH >= 4 ? 1 : 2;
   const size_t lds = skew_ph_lds(16 * NCH, 32 * NT);
   const int64_t passes = ((int64_t)1 << op.nM) / kSkewPM;
   const dim3 g((unsigned)std::min<int64_t>(passes, 512));
-  hipLaunchKernelGGL((k_skew_ph<NT, VEC, NCH, PD, E>), g, dim3(256), lds, s, A, B, C, op, mp, maxslot);
+  hipLaunchKernelGGL((k_skew_ph<NT, VEC, MODE, NCH, PD, E>), g, dim3(256), lds, s, A, B, C, op, mp, maxslot);
   return hipGetLastError();
 }
 
-// 16-bit storage with 16 <= K <= 64: the half-precision matrix cores
-template <int NT, typename E>
-static hipError_t launch_skew_h(const E* A, const E* B, E* C, const IndexOp& op, float* maxslot, hipStream_t s) {
-  constexpr int VEC = 16 / (int)sizeof(E);
-  SkewMap mp{};
-  if (!skew_map(op, 4, 2, &mp)) return hipErrorInvalidValue;
-  const bool vec = mp.pos[0] == 0 && mp.pos[1] == 1;
-  if (vec) {
-    switch (op.nK) {
-      case 4: return launch_skew_half<NT, VEC, 1, E>(A, B, C, op, mp, maxslot, s);
-      case 5: return launch_skew_half<NT, VEC, 2, E>(A, B, C, op, mp, maxslot, s);
-      default: return launch_skew_half<NT, VEC, 4, E>(A, B, C, op, mp, maxslot, s);
-    }
-  }
+template <int NT, int VEC, int MODE, typename E>
+static hipError_t launch_skew_hn(const E* A, const E* B, E* C, const IndexOp& op, const SkewMap& mp, float* maxslot,
+                                 hipStream_t s) {
   switch (op.nK) {
-    case 4: return launch_skew_half<NT, 1, 1, E>(A, B, C, op, mp, maxslot, s);
-    case 5: return launch_skew_half<NT, 1, 2, E>(A, B, C, op, mp, maxslot, s);
-    default: return launch_skew_half<NT, 1, 4, E>(A, B, C, op, mp, maxslot, s);
+    case 4: return launch_skew_half<NT, VEC, MODE, 1, E>(A, B, C, op, mp, maxslot, s);
+    case 5: return launch_skew_half<NT, VEC, MODE, 2, E>(A, B, C, op, mp, maxslot, s);
+    case 6: return launch_skew_half<NT, VEC, MODE, 4, E>(A, B, C, op, mp, maxslot, s);
+    default: break;
   }
-}
-
-// 16-bit storage with 128 <= K <= 2^10: B staged chunk by chunk
-template <int NT, typename E>
-static hipError_t launch_skew_hc(const E* A, const E* B, E* C, const IndexOp& op, float* maxslot, hipStream_t s) {
-  constexpr int VEC = 16 / (int)sizeof(E);
-  SkewMap mp{};
-  if (!skew_map(op, 4, 2, &mp)) return hipErrorInvalidValue;
+  // 128 <= K <= 2^10: B staged chunk by chunk
   const int64_t passes = ((int64_t)1 << op.nM) / kSkewPM;
   const dim3 g((unsigned)std::min<int64_t>(passes, 512));
-  if (mp.pos[0] == 0 && mp.pos[1] == 1)
-    hipLaunchKernelGGL((k_skew_phc<NT, VEC, E>), g, dim3(256), 0, s, A, B, C, op, mp, maxslot);
-  else
-    hipLaunchKernelGGL((k_skew_phc<NT, 1, E>), g, dim3(256), 0, s, A, B, C, op, mp, maxslot);
+  hipLaunchKernelGGL((k_skew_phc<NT, VEC, MODE, E>), g, dim3(256), 0, s, A, B, C, op, mp, maxslot);
   return hipGetLastError();
+}
+
+// 16-bit storage with 16 <= K <= 2^10: the half-precision matrix cores
+template <int NT, typename E>
+static hipError_t launch_skew_h(const E* A, const E* B, E* C, const IndexOp& op, float* maxslot, hipStream_t s) {
+  SkewMap mp{};
+  if (!skew_map(op, 4, 2, &mp)) return hipErrorInvalidValue;
+  SkewMap q = mp;
+  switch (quad_mode(&q, 1)) {
+    case kQuadKK: return launch_skew_hn<NT, 4, kQuadKK, E>(A, B, C, op, q, maxslot, s);
+    case kQuadKR: return launch_skew_hn<NT, 4, kQuadKR, E>(A, B, C, op, q, maxslot, s);
+    case kQuadRK: return launch_skew_hn<NT, 4, kQuadRK, E>(A, B, C, op, q, maxslot, s);
+    case kQuadRR: return launch_skew_hn<NT, 4, kQuadRR, E>(A, B, C, op, q, maxslot, s);
+    default: return launch_skew_hn<NT, 1, kQuadKK, E>(A, B, C, op, mp, maxslot, s);
+  }
 }
 
 template <typename E>
 static hipError_t launch_skew_e(const E* A, const E* B, E* C, const IndexOp& op, float* maxslot, hipStream_t s) {
   if constexpr (sizeof(E) == 4) {
-    if (op.nK >= 4 && op.nK <= 6) {
+    if (op.nK >= 4) {
       if (op.nN <= 5) return launch_skew_h<1, E>(A, B, C, op, maxslot, s);
       return launch_skew_h<2, E>(A, B, C, op, maxslot, s);
-    }
-    if (op.nK >= 7 && op.nK <= 10) {
-      if (op.nN <= 5) return launch_skew_hc<1, E>(A, B, C, op, maxslot, s);
-      return launch_skew_hc<2, E>(A, B, C, op, maxslot, s);
     }
   }
   if (op.nN <= 5) return launch_skew_t<1, E>(A, B, C, op, maxslot, s);
