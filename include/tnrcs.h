@@ -263,7 +263,8 @@ int tn_plan_info(tn_plan_t p, tn_plan_stats* s);
  * kernel class (1 GEMM, 2 gathered, 3 skewed, 4 split-K), its
  * relabelled layout key and whether the class tuner chose it; "small_net":
  * whether slices run as one launch each from on-chip memory instead of those
- * kernels) into buf (capacity cap bytes, NUL-terminated);
+ * kernels; "fused_out": whether a pairwise plan's last kernel also does the
+ * permute listed after it) into buf (capacity cap bytes, NUL-terminated);
  * *needed receives the full length + 1.  buf may be NULL to query the size. */
 int tn_plan_json(tn_plan_t p, char* buf, int64_t cap, int64_t* needed);
 

@@ -332,6 +332,28 @@ static int launch_op(tn_plan_s* p, const Op& op, hipStream_t s) {
   return TN_OK;
 }
 
+// The last step of a pairwise plan and its output permute in one kernel.
+static int launch_fused(tn_plan_s* p, hipStream_t s) {
+  const FusedOut& F = p->core.fused;
+  const Op& op = p->core.ops[F.op];
+  const int dt = p->core.opts.dtype;
+  const char* a = resolve(p, op.a);
+  const char* b = resolve(p, op.b);
+  char* c = resolve(p, p->core.ops[F.op + 1].c);
+  float* slot = op.max_slot >= 0 ? p->d_maxslots + op.max_slot : nullptr;
+  IndexOp idx = F.idx;
+  idx.out_scale = op.idx.out_scale;
+  if (op.kind == kOpSkew)
+    HIP_TRY(launch_skew(dt, a, b, c, idx, slot, s, &F.out), "skewed contraction kernel (C in place)");
+  else if (dt == TN_DTYPE_C64)
+    HIP_TRY(launch_gemm_c64_ga((const float2*)a, (const float2*)b, (float2*)c, idx, op.gemm.form, s, &F.out),
+            "gemm kernel (C in place)");
+  else
+    HIP_TRY(launch_gemm_half_ga(dt, a, b, c, idx, op.gemm.out_scale, slot, s, &F.out),
+            "half gemm kernel (C in place)");
+  return TN_OK;
+}
+
 static int launch_bind_slice(tn_plan_s* p, hipStream_t s) {
   const PlanCore& P = p->core;
   if (!P.binds.empty())
@@ -818,10 +840,13 @@ int tn_pair_run(tn_plan_t p, const void* A, const void* B, void* C, int64_t batc
     p->ext_a = (const char*)A + i * sa;
     p->ext_b = (const char*)B + i * sb;
     p->ext_c = (char*)C + i * sc;
-    for (const Op& op : P.ops) {
-      int rc = launch_op(p, op, s);
+    const int n = (int)P.ops.size() - (P.fused.ok ? 2 : 0);
+    for (int j = 0; j < n; ++j) {
+      int rc = launch_op(p, P.ops[j], s);
       if (rc) return rc;
     }
+    if (P.fused.ok)
+      if (int rc = launch_fused(p, s)) return rc;
   }
   p->last_stream = s;
   p->ran = true;

@@ -8,6 +8,7 @@
 #include "elem.h"
 #include "gather.h"
 #include "kernels.h"
+#include "outmap.h"
 
 namespace tnrcs {
 
@@ -148,16 +149,17 @@ struct GatherA {
 // keeps the kernel within 256 registers per lane (two waves per SIMD).
 // blockIdx.z selects a batch entry or a split-K slab through the strides sA,
 // sB, sC (GA = 0 only).
-template <int FORM, int GA>
+template <int FORM, int GA, typename OM>
 __global__ __launch_bounds__(256, 2) void k_cgemm128(const float2* __restrict__ A, const float2* __restrict__ B,
                                                  float2* __restrict__ C, int64_t N, int64_t K, int64_t k_len,
                                                  int64_t sA, int64_t sB, int64_t sC, int64_t Mt, int64_t Nt,
-                                                 int chunk, const GatherA g) {
+                                                 int chunk, const GatherA g, const OM om) {
   constexpr int P = (FORM == TN_GEMM_3M) ? 3 : 2;
   constexpr int BM = 128, BN = 128, BK = 16, LD = BM + 2;
   constexpr int LPT = 4;  // gathered A: 16-byte loads per thread per chunk
-  __shared__ float As[2][BK][LD];
-  __shared__ float Bs[2][BK][LD];
+  __shared__ __attribute__((aligned(16))) float AB[2][2][BK][LD];
+  float (*As)[BK][LD] = AB[0];
+  float (*Bs)[BK][LD] = AB[1];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int64_t tm, tn, z;
   xcd_tile(blockIdx.x, Mt, Nt, gridDim.x, tm, tn, z);
@@ -175,7 +177,9 @@ __global__ __launch_bounds__(256, 2) void k_cgemm128(const float2* __restrict__ 
       for (int j = 0; j < 2; ++j) acc[p][i][j] = floatx16{};
   const int lrow = tid >> 1, lk = (tid & 1) * 8;
   const float2* Ap = A + (bm + lrow) * K + lk;
-  const float2* Bp = B + (bn + lrow) * K + lk;
+  int64_t brow_b = bn + lrow;
+  if constexpr (has_out<OM>) brow_b = (int64_t)dep((uint64_t)brow_b, om.nmap);
+  const float2* Bp = B + brow_b * K + lk;
   float4 ra[4], rb[4];
   // gathered A: this thread's two entries per load (offset of the first
   // from the chunk's first entry; LDS indices k * LD + m of both, packed in
@@ -330,6 +334,36 @@ __global__ __launch_bounds__(256, 2) void k_cgemm128(const float2* __restrict__ 
         }
     }
   }
+  if constexpr (has_out<OM>) {
+    // (sums of at most one chunk: nothing has been stored yet.)  Blocks (i, j)
+    // of all four waves: one sub-tile in C's order at a time
+    float2* Cs = reinterpret_cast<float2*>(&AB[0][0][0][0]);
+    const int at = out_lane(om, c, kh) ^ (wave & 1 ? om.srow[6] : 0) ^ (wave >> 1 ? om.scol[6] : 0);
+    const uint64_t tile = dep_u<12>((uint64_t)bm, om.cM) | dep_u<12>((uint64_t)bn, om.cN);
+    const uint64_t toff = out_thread<float2>(om, tid);
+    const uint64_t oi = dep_u<12>(32, om.cM), oj = dep_u<12>(32, om.cN);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          float2 v;
+          if (FORM == TN_GEMM_3M) {
+            v.x = acc[0][i][j][r] - acc[1][i][j][r];
+            v.y = acc[P - 1][i][j][r] - acc[0][i][j][r] - acc[1][i][j][r];
+          } else {
+            v.x = acc[0][i][j][r];
+            v.y = acc[1][i][j][r];
+          }
+          Cs[at ^ out_reg(om, r)] = v;
+        }
+        __syncthreads();
+        out_write<float2, 12>(om, C, Cs, tile | (i ? oi : 0) | (j ? oj : 0), toff, tid);
+      }
+    return;
+  }
   if (first)
     flush(std::false_type{});
   else
@@ -385,11 +419,11 @@ hipError_t launch_gemm_c64(const float2* A, const float2* B, float2* C, int64_t 
     const int64_t Mt = M / 128, Nt = N / 128;
     dim3 grid((unsigned)(Mt * Nt * splits));
     if (form == TN_GEMM_3M)
-      hipLaunchKernelGGL((k_cgemm128<TN_GEMM_3M, 0>), grid, dim3(256), 0, s, A, B, work, N, K, kl, kl, kl, M * N, Mt, Nt,
-                         chunk, GatherA{});
+      hipLaunchKernelGGL((k_cgemm128<TN_GEMM_3M, 0, NoOut>), grid, dim3(256), 0, s, A, B, work, N, K, kl, kl, kl, M * N, Mt, Nt,
+                         chunk, GatherA{}, NoOut{});
     else
-      hipLaunchKernelGGL((k_cgemm128<TN_GEMM_4M, 0>), grid, dim3(256), 0, s, A, B, work, N, K, kl, kl, kl, M * N, Mt, Nt,
-                         chunk, GatherA{});
+      hipLaunchKernelGGL((k_cgemm128<TN_GEMM_4M, 0, NoOut>), grid, dim3(256), 0, s, A, B, work, N, K, kl, kl, kl, M * N, Mt, Nt,
+                         chunk, GatherA{}, NoOut{});
     hipLaunchKernelGGL(k_splitk_sum, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 8192)), dim3(256), 0, s,
                        work, C, n, splits);
     return hipGetLastError();
@@ -401,11 +435,11 @@ hipError_t launch_gemm_c64(const float2* A, const float2* B, float2* C, int64_t 
     const int64_t Mt = M / 128, Nt = N / 128;
     dim3 grid((unsigned)(Mt * Nt * batch));
     if (form == TN_GEMM_3M)
-      hipLaunchKernelGGL((k_cgemm128<TN_GEMM_3M, 0>), grid, dim3(256), 0, s, A, B, C, N, K, K, M * K, N * K, M * N, Mt, Nt,
-                         chunk, GatherA{});
+      hipLaunchKernelGGL((k_cgemm128<TN_GEMM_3M, 0, NoOut>), grid, dim3(256), 0, s, A, B, C, N, K, K, M * K, N * K, M * N, Mt, Nt,
+                         chunk, GatherA{}, NoOut{});
     else
-      hipLaunchKernelGGL((k_cgemm128<TN_GEMM_4M, 0>), grid, dim3(256), 0, s, A, B, C, N, K, K, M * K, N * K, M * N, Mt, Nt,
-                         chunk, GatherA{});
+      hipLaunchKernelGGL((k_cgemm128<TN_GEMM_4M, 0, NoOut>), grid, dim3(256), 0, s, A, B, C, N, K, K, M * K, N * K, M * N, Mt, Nt,
+                         chunk, GatherA{}, NoOut{});
     return hipGetLastError();
   }
   if (N / GBN > 65535) return hipErrorInvalidValue;
@@ -426,7 +460,7 @@ static uint64_t dep_host(uint64_t x, const Runs& r) {
 }
 
 hipError_t launch_gemm_c64_ga(const float2* A, const float2* B, float2* C, const IndexOp& idx, int form,
-                              hipStream_t s) {
+                              hipStream_t s, const OutMap* out) {
   if (!gemm_gather_ok(idx)) return hipErrorInvalidValue;
   const int64_t M = (int64_t)1 << idx.nM, N = (int64_t)1 << idx.nN, K = (int64_t)1 << idx.nK;
   GatherA g{};
@@ -438,10 +472,18 @@ hipError_t launch_gemm_c64_ga(const float2* A, const float2* B, float2* C, const
   const int chunk = kAccChain / 16;
   const int64_t Mt = M / 128, Nt = N / 128;
   const dim3 grid((unsigned)(Mt * Nt));
-  if (form == TN_GEMM_3M)
-    hipLaunchKernelGGL((k_cgemm128<TN_GEMM_3M, 1>), grid, dim3(256), 0, s, A, B, C, N, K, K, 0, 0, 0, Mt, Nt, chunk, g);
+  if (out && form == TN_GEMM_3M)
+    hipLaunchKernelGGL((k_cgemm128<TN_GEMM_3M, 1, OutMap>), grid, dim3(256), 0, s, A, B, C, N, K, K, 0, 0, 0, Mt, Nt,
+                       chunk, g, *out);
+  else if (out)
+    hipLaunchKernelGGL((k_cgemm128<TN_GEMM_4M, 1, OutMap>), grid, dim3(256), 0, s, A, B, C, N, K, K, 0, 0, 0, Mt, Nt,
+                       chunk, g, *out);
+  else if (form == TN_GEMM_3M)
+    hipLaunchKernelGGL((k_cgemm128<TN_GEMM_3M, 1, NoOut>), grid, dim3(256), 0, s, A, B, C, N, K, K, 0, 0, 0, Mt, Nt,
+                       chunk, g, NoOut{});
   else
-    hipLaunchKernelGGL((k_cgemm128<TN_GEMM_4M, 1>), grid, dim3(256), 0, s, A, B, C, N, K, K, 0, 0, 0, Mt, Nt, chunk, g);
+    hipLaunchKernelGGL((k_cgemm128<TN_GEMM_4M, 1, NoOut>), grid, dim3(256), 0, s, A, B, C, N, K, K, 0, 0, 0, Mt, Nt,
+                       chunk, g, NoOut{});
   return hipGetLastError();
 }
 

@@ -17,6 +17,7 @@
 #include "elem.h"
 #include "gather.h"
 #include "kernels.h"
+#include "outmap.h"
 
 namespace tnrcs {
 
@@ -387,15 +388,16 @@ struct GatherAH {
   uint64_t maskK = 0, incK = 0;
 };
 
-template <int MODE, typename H, typename E>
+template <int MODE, typename H, typename E, typename OM>
 __global__ __launch_bounds__(256, 2) void k_hgemm_ga(const E* __restrict__ A, const E* __restrict__ B,
                                                    E* __restrict__ C, int64_t N, int64_t K, float out_scale,
-                                                   float* maxslot, int64_t Mt, int64_t Nt, const GatherAH g) {
+                                                   float* maxslot, int64_t Mt, int64_t Nt, const GatherAH g, const OM om) {
   typedef typename Frag<H>::T F;
   constexpr int BK = 32, BM = 128, BN = 128, LDK = BK + 8, P = 2, WTM = 2, WTN = 2;
   constexpr int NVB = BK / (256 / BN) / 4;  // B: uint4 loads per thread per stage
-  __shared__ __attribute__((aligned(16))) H As[2][P][BM][LDK];
-  __shared__ __attribute__((aligned(16))) H Bs[2][P][BN][LDK];
+  __shared__ __attribute__((aligned(16))) H AB[4 * P * BM * LDK];
+  H (*As)[P][BM][LDK] = reinterpret_cast<H (*)[P][BM][LDK]>(AB);
+  H (*Bs)[P][BN][LDK] = reinterpret_cast<H (*)[P][BN][LDK]>(AB + 2 * P * BM * LDK);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int64_t tm, tn, z;
   xcd_tile(blockIdx.x, Mt, Nt, gridDim.x, tm, tn, z);
@@ -426,7 +428,9 @@ __global__ __launch_bounds__(256, 2) void k_hgemm_ga(const E* __restrict__ A, co
   const uint64_t abase = dep_u<12>((uint64_t)bm, g.aM);
   uint64_t kofs = 0;
   const int brow = tid / 2, bk = (tid % 2) * 16;
-  const uint4* Bp = reinterpret_cast<const uint4*>(B + (bn + brow) * K + bk);
+  int64_t brow_b = bn + brow;
+  if constexpr (has_out<OM>) brow_b = (int64_t)dep((uint64_t)brow_b, om.nmap);
+  const uint4* Bp = reinterpret_cast<const uint4*>(B + brow_b * K + bk);
   uint4 ra[4], rb[NVB];
   auto load_a = [&]() {
     const E* base = A + (abase + kofs);
@@ -534,6 +538,29 @@ __global__ __launch_bounds__(256, 2) void k_hgemm_ga(const E* __restrict__ A, co
   }
   float mx = 0.f;
   const int kh = lane >> 5;
+  if constexpr (has_out<OM>) {
+    // the whole tile in C's order (64 KB, over the idle stage buffers)
+    E* Cs = reinterpret_cast<E*>(AB);
+    const int at = out_lane(om, c, kh) ^ (wave & 1 ? om.srow[6] : 0) ^ (wave >> 1 ? om.scol[6] : 0);
+#pragma unroll
+    for (int i = 0; i < WTM; ++i)
+#pragma unroll
+      for (int j = 0; j < WTN; ++j) {
+        const int aij = at ^ (i ? om.srow[5] : 0) ^ (j ? om.scol[5] : 0);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const float re = acc[0][i][j][r], im = acc[1][i][j][r];
+          mx = mag_max(mx, re, im);
+          Cs[aij ^ out_reg(om, r)] = from_f2<E>(re * out_scale, im * out_scale);
+        }
+      }
+    __syncthreads();
+    out_write<E, 14>(om, C, Cs, dep_u<12>((uint64_t)bm, om.cM) | dep_u<12>((uint64_t)bn, om.cN), out_thread<E>(om, tid),
+                     tid);
+    __syncthreads();
+    record_max_in(maxslot, mx, reinterpret_cast<float*>(&As[0][0][0][0]));
+    return;
+  }
 #pragma unroll
   for (int i = 0; i < WTM; ++i)
 #pragma unroll
@@ -558,15 +585,19 @@ static uint64_t dep_host_h(uint64_t x, const Runs& r) {
 
 template <int MODE, typename H, typename E>
 static void hgemm_ga_launch(const E* A, const E* B, E* C, int64_t M, int64_t N, int64_t K, float scale,
-                            float* maxslot, const GatherAH& g, hipStream_t s) {
+                            float* maxslot, const GatherAH& g, const OutMap* out, hipStream_t s) {
   const int64_t Mt = M / 128, Nt = N / 128;
-  hipLaunchKernelGGL((k_hgemm_ga<MODE, H, E>), dim3((unsigned)(Mt * Nt)), dim3(256), 0, s, A, B, C, N, K, scale,
-                     maxslot, Mt, Nt, g);
+  if (out)
+    hipLaunchKernelGGL((k_hgemm_ga<MODE, H, E, OutMap>), dim3((unsigned)(Mt * Nt)), dim3(256), 0, s, A, B, C, N, K,
+                       scale, maxslot, Mt, Nt, g, *out);
+  else
+    hipLaunchKernelGGL((k_hgemm_ga<MODE, H, E, NoOut>), dim3((unsigned)(Mt * Nt)), dim3(256), 0, s, A, B, C, N, K,
+                       scale, maxslot, Mt, Nt, g, NoOut{});
 }
 
 template <typename H, typename E>
 static hipError_t hgemm_ga_t(const E* A, const E* B, E* C, const IndexOp& idx, float scale, float* maxslot,
-                             hipStream_t s) {
+                             const OutMap* out, hipStream_t s) {
   const int64_t M = (int64_t)1 << idx.nM, N = (int64_t)1 << idx.nN, K = (int64_t)1 << idx.nK;
   GatherAH g{};
   if (!skew_map(idx, 5, 0, &g.mp) || g.mp.v != 12) return hipErrorInvalidValue;
@@ -574,22 +605,22 @@ static hipError_t hgemm_ga_t(const E* A, const E* B, E* C, const IndexOp& idx, f
   g.maskK = dep_host_h((uint64_t)(K - 1) & ~(uint64_t)31, idx.aK);
   g.incK = K > 32 ? dep_host_h(32, idx.aK) : 0;
   switch (quad_mode(&g.mp, 2)) {
-    case kQuadKK: hgemm_ga_launch<kQuadKK, H, E>(A, B, C, M, N, K, scale, maxslot, g, s); break;
-    case kQuadKR: hgemm_ga_launch<kQuadKR, H, E>(A, B, C, M, N, K, scale, maxslot, g, s); break;
-    case kQuadRK: hgemm_ga_launch<kQuadRK, H, E>(A, B, C, M, N, K, scale, maxslot, g, s); break;
-    case kQuadRR: hgemm_ga_launch<kQuadRR, H, E>(A, B, C, M, N, K, scale, maxslot, g, s); break;
+    case kQuadKK: hgemm_ga_launch<kQuadKK, H, E>(A, B, C, M, N, K, scale, maxslot, g, out, s); break;
+    case kQuadKR: hgemm_ga_launch<kQuadKR, H, E>(A, B, C, M, N, K, scale, maxslot, g, out, s); break;
+    case kQuadRK: hgemm_ga_launch<kQuadRK, H, E>(A, B, C, M, N, K, scale, maxslot, g, out, s); break;
+    case kQuadRR: hgemm_ga_launch<kQuadRR, H, E>(A, B, C, M, N, K, scale, maxslot, g, out, s); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
 hipError_t launch_gemm_half_ga(int dtype, const void* A, const void* B, void* C, const IndexOp& idx, float out_scale,
-                               float* maxslot, hipStream_t s) {
+                               float* maxslot, hipStream_t s, const OutMap* out) {
   if (!gemm_gather_ok(idx) || idx.nK < 5) return hipErrorInvalidValue;
   if (dtype == TN_DTYPE_F16S)
-    return hgemm_ga_t<_Float16, cf16>((const cf16*)A, (const cf16*)B, (cf16*)C, idx, out_scale, maxslot, s);
+    return hgemm_ga_t<_Float16, cf16>((const cf16*)A, (const cf16*)B, (cf16*)C, idx, out_scale, maxslot, out, s);
   if (dtype == TN_DTYPE_BF16S)
-    return hgemm_ga_t<__bf16, cbf16>((const cbf16*)A, (const cbf16*)B, (cbf16*)C, idx, out_scale, maxslot, s);
+    return hgemm_ga_t<__bf16, cbf16>((const cbf16*)A, (const cbf16*)B, (cbf16*)C, idx, out_scale, maxslot, out, s);
   return hipErrorInvalidValue;
 }
 

@@ -71,6 +71,37 @@ struct IndexOp {
   float out_scale = 1.f;  // scaled storage: 2^-s applied before rounding
 };
 
+// Output written in a caller's index order (pairwise plans): a kernel stages
+// a sub-tile of its outputs in LDS in the order of their positions in C, and
+// writes it in 16-byte runs.  A sub-tile has (up to) 7 row and 7 column bits
+// of the kernel's tile; entry (row, col) sits at LDS entry
+// XOR of srow[b], scol[b] over the set bits, which is swizzle(f) for its rank
+// f in C's order; f bit i is position cpos[i] of C.  cM, cN: position in C of
+// every row and column bit.
+constexpr int kOutMaxBits = 14;
+struct OutMap {
+  int32_t bits = 0;  // f bits of a sub-tile
+  int16_t srow[7] = {}, scol[7] = {};
+  int8_t cpos[kOutMaxBits] = {};
+  Runs cM, cN;
+  Runs nmap;  // GEMM: column bit -> bit of B's row index
+};
+// LDS swizzle of f (lv = log2 of the entries in 16 bytes): bits 6 .. 10 and
+// 11 .. 13 are added to the five bits above lv, so that entries far apart in C's order
+// that one store instruction writes fall into different banks.  Linear over
+// XOR, and each bit only takes part of higher ones: a bijection.
+inline constexpr uint32_t out_swizzle(uint32_t f, int lv) {
+  return f ^ ((((f >> 6) & 31u) ^ ((f >> 11) & 7u)) << lv);
+}
+
+// A pairwise plan's last step with its output permute done by the kernel.
+struct FusedOut {
+  bool ok = false;
+  int32_t op = -1;  // the producing op (the permute follows it)
+  IndexOp idx;      // its index maps with the row and column bits reordered
+  OutMap out;
+};
+
 struct Op {
   int32_t kind = kOpGeneric;
   int32_t step = -1;  // SSA step this op belongs to
@@ -202,6 +233,7 @@ struct PlanCore {
 
   // pairwise-contraction mode (one step A x B -> C over caller buffers)
   bool pair_mode = false;
+  FusedOut fused;  // the last step's kernel also does the output permute that follows it
   std::vector<int> pair_a, pair_b, pair_out;  // index labels, most significant first
 };
 
@@ -209,6 +241,11 @@ struct PlanCore {
 // labels (most significant first); the result is left in kExtC in the order
 // of `out` (a permute is appended when the step's natural layout differs).
 int build_pair_plan(PlanCore& P, std::string& err);
+// Fills F when the plan's last op permutes the output of a GEMM that reads A
+// in place or of a skewed step, and that kernel can write C's order itself.
+void plan_fused_out(const PlanCore& P, FusedOut* F);
+// Whether the skewed kernel of these extents can (skew.hip).
+bool skew_out_ok(int dtype, const IndexOp& op);
 // (Re)writes P.json from the current plan.
 void make_json(PlanCore& P);
 

@@ -491,30 +491,14 @@ __global__ __launch_bounds__(256) void k_generic_tiled(const E* __restrict__ A, 
   const int nk = 1 << op.nK;
   const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
   const int64_t tiles_n = (int64_t)1 << (op.nN - 6), tiles = (int64_t)1 << (op.nM + op.nN - 12);
-  // this thread gathers row r of both operands at k = kq, kq + 4, ...
-  const int r = tid & 63, kq = tid >> 6;
-  const uint64_t ar = dep((uint64_t)r, op.aM), br = dep((uint64_t)r, op.bN);
-  uint64_t ak[4], bk[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    ak[q] = bk[q] = 0;
-    if (4 * q < nk) {
-      ak[q] = ar | dep((uint64_t)(kq + 4 * q), op.aK);
-      bk[q] = br | dep((uint64_t)(kq + 4 * q), op.bK);
-    }
-  }
   float mx = 0.f;
   for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
     const int64_t m0 = (t / tiles_n) << 6, n0 = (t % tiles_n) << 6;
-    const E* At = A + dep((uint64_t)m0, op.aM);
-    const E* Bt = B + dep((uint64_t)n0, op.bN);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int k = kq + 4 * q;
-      if (k < nk) {
-        As[k][r] = to_f2(At[ak[q]]);
-        Bs[k][r] = to_f2(Bt[bk[q]]);
-      }
+    for (int i = tid; i < 64 * nk; i += 256) {
+      const int k = i >> 6, r = i & 63;
+      const uint64_t ak = dep((uint64_t)k, op.aK), bk = dep((uint64_t)k, op.bK);
+      As[k][r] = to_f2(A[dep((uint64_t)(m0 + r), op.aM) | ak]);
+      Bs[k][r] = to_f2(B[dep((uint64_t)(n0 + r), op.bN) | bk]);
     }
     __syncthreads();
     float re[4][4], im[4][4];

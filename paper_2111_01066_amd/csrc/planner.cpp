@@ -334,7 +334,7 @@ void make_json(PlanCore& P) {
     js << (i ? "," : "") << "{\"t\":" << st.t << ",\"nM\":" << st.nM << ",\"nN\":" << st.nN << ",\"nK\":" << st.nK
        << ",\"cls\":" << st.cls << ",\"key\":\"" << st.key << "\",\"tuned\":" << (P.class_override.count(st.t) ? "true" : "false") << "}";
   }
-  js << "],\"small_net\":" << (P.small.ok ? "true" : "false") << ",\"accum\":{\"n_open\":" << P.accum.n_open << ",\"root\":";
+  js << "],\"small_net\":" << (P.small.ok ? "true" : "false") << ",\"fused_out\":" << (P.fused.ok ? "true" : "false") << ",\"accum\":{\"n_open\":" << P.accum.n_open << ",\"root\":";
   json_ref(js, P.accum.root);
   js << ",\"y2root\":";
   json_runs(js, P.accum.y2root);
@@ -1088,8 +1088,152 @@ int build_pair_plan(PlanCore& P, std::string& err) {
     P.stats.moved_per_slice += op.bytes;
   }
   P.stats.n_kernels = (int)P.ops.size();
+  plan_fused_out(P, &P.fused);
   make_json(P);
   return TN_OK;
+}
+
+void plan_fused_out(const PlanCore& P, FusedOut* F) {
+  *F = FusedOut{};
+  const int n_ops = (int)P.ops.size();
+  if (!P.pair_mode || n_ops < 2 || P.ops[n_ops - 1].kind != kOpPermute) return;
+  const Op& perm = P.ops[n_ops - 1];
+  const Op& op = P.ops[n_ops - 2];
+  const bool half = P.opts.dtype != TN_DTYPE_C64;
+  const bool gemm = op.kind == kOpGemm && op.gemm.gather_a;
+  if (!gemm && op.kind != kOpSkew) return;
+  // A skewed step reads A in shorter runs when its row tile also serves C's
+  // order: worth it while A is at most four times C (2^22 rows, K = 32, 16
+  // columns in complex64: 357 us against 550 with the permute; 2^20 rows, K =
+  // 512, 32 columns in FP16: 961 against 705).
+  if (!gemm && op.idx.nK > op.idx.nN + 2) return;
+  const bool whole = gemm && half;  // the 16-bit GEMM's LDS holds the whole tile
+  if (op.c.region != perm.a.region || op.c.off != perm.a.off) return;
+  IndexOp idx = op.idx;
+  if (gemm) {
+    idx.nN = 0;
+    while (((int64_t)1 << idx.nN) < op.gemm.N) ++idx.nN;
+  }
+  const int nM = idx.nM, nN = idx.nN;
+  if (nM < 7) return;
+  // position in C of the natural layout's bit p ([row bits, column bits])
+  std::vector<int> cpos(nM + nN);
+  for (int q = 0; q < nM + nN; ++q) cpos[perm.perm.perm[q]] = q;
+  std::vector<int> am(nM), cm(nM), cn(nN);  // row bits: A and C positions; column bits: C positions
+  for (int j = 0; j < nM; ++j) {
+    am[j] = run_pos(idx.aM, j);
+    cm[j] = cpos[nN + j];
+    if (am[j] < 0) return;
+  }
+  for (int j = 0; j < nN; ++j) cn[j] = cpos[j];
+  // The 7 row bits of a tile: the bit that ends the shorter of the two runs of
+  // consecutive positions, A's and C's, until there are 7; the least wanted one is
+  // bit 5 (the complex64 GEMM stages the two 32-row blocks of a wave's rows
+  // one after the other).  The other row bits follow in A's order.
+  std::vector<int> tile;
+  auto take = [&](int j) {
+    if ((int)tile.size() < 7 && std::find(tile.begin(), tile.end(), j) == tile.end()) tile.push_back(j);
+  };
+  std::vector<int> row_at_a(kMaxRank, -1), row_at_c(kMaxRank, -1);
+  for (int j = 0; j < nM; ++j) {
+    row_at_a[am[j]] = j;
+    row_at_c[cm[j]] = j;
+  }
+  const int n_tile = gemm ? 7 : std::min(nN, 7);  // columns in the tile: C's lowest
+  std::vector<int> cn_sorted = cn;
+  std::sort(cn_sorted.begin(), cn_sorted.end());
+  // runs so far: all positions below run_a / run_c are in the tile (A's k bits
+  // below the chunk's are, since the chunk holds the lowest ones)
+  const int n_chunk = std::min(idx.nK, gemm && half ? 5 : 4);
+  std::vector<int> ak;
+  for (int j = 0; j < idx.nK; ++j) ak.push_back(run_pos(idx.aK, j));
+  std::sort(ak.begin(), ak.end());
+  int run_a = 0, run_c = 0;
+  const int need = half ? 4 : 3;  // runs of 64 bytes
+  auto grow = [&](int& run, const std::vector<int>& row_at, const std::vector<int>& others, int n_others) {
+    // passes over what is in the tile; the row bit it stops at, or -1
+    while (run < kMaxRank) {
+      const int j = row_at[run];
+      const bool other = std::find(others.begin(), others.begin() + n_others, run) != others.begin() + n_others;
+      if (other || (j >= 0 && std::find(tile.begin(), tile.end(), j) != tile.end()))
+        ++run;
+      else
+        return j;
+    }
+    return -1;
+  };
+  while ((int)tile.size() < 7) {
+    const int ja = grow(run_a, row_at_a, ak, n_chunk), jc = grow(run_c, row_at_c, cn_sorted, std::min(n_tile, nN));
+    if (ja < 0 && jc < 0) break;
+    take(jc >= 0 && (ja < 0 || run_c < run_a || (run_c == run_a && run_a >= need)) ? jc : ja);
+  }
+  std::vector<int> by_a(nM);
+  for (int j = 0; j < nM; ++j) by_a[j] = j;
+  std::sort(by_a.begin(), by_a.end(), [&](int x, int y) { return am[x] < am[y]; });
+  for (int j : by_a) take(j);
+  // both sides in runs of 64 bytes at least (19 row, 5 column and 6 contracted
+  // bits in FP16 with A in runs of 32 bytes: 149 us, 116 with the permute, 93 in
+  // runs of 64)
+  grow(run_a, row_at_a, ak, n_chunk);
+  grow(run_c, row_at_c, cn_sorted, std::min(n_tile, nN));
+  if (run_a < need || run_c < need) return;
+  std::vector<int> rows = tile;
+  std::sort(rows.begin(), rows.end(), [&](int x, int y) { return am[x] < am[y]; });
+  if (gemm) {
+    rows.erase(std::find(rows.begin(), rows.end(), tile.back()));
+    rows.insert(rows.begin() + 5, tile.back());
+  }
+  for (int j : by_a)
+    if (std::find(tile.begin(), tile.end(), j) == tile.end()) rows.push_back(j);
+  // columns: C's lowest positions first; bit 5 (a GEMM's 64-column halves, a
+  // skewed step's second block of 32) is the least wanted of the tile's
+  std::vector<int> cols(nN);
+  for (int j = 0; j < nN; ++j) cols[j] = j;
+  std::sort(cols.begin(), cols.end(), [&](int x, int y) { return cn[x] < cn[y]; });
+  if (gemm && nN >= 7) std::swap(cols[5], cols[6]);
+  OutMap& o = F->out;
+  // sub-tile bits: all tile bits but, where the tile is staged in parts, row
+  // bit 5 (GEMM) and column bit 5
+  struct Bit {
+    int c, row, col;
+  };
+  std::vector<Bit> bits;
+  for (int b = 0; b < 7; ++b)
+    if (whole || !gemm || b != 5) bits.push_back({cm[rows[b]], b, -1});
+  for (int b = 0; b < std::min(nN, 7); ++b)
+    if (whole || b != 5) bits.push_back({cn[cols[b]], -1, b});
+  if ((int)bits.size() > kOutMaxBits) return;
+  std::sort(bits.begin(), bits.end(), [](const Bit& x, const Bit& y) { return x.c < y.c; });
+  // 16-byte stores: the sub-tile's lowest bits are C's (the bits left out of
+  // a staged part are its highest)
+  const int lv = half ? 2 : 1;
+  o.bits = (int)bits.size();
+  if (o.bits < lv + 2) return;
+  for (int i = 0; i <= lv; ++i)
+    if (bits[i].c != i) return;
+  for (int i = 0; i < o.bits; ++i) {
+    o.cpos[i] = (int8_t)bits[i].c;
+    const int16_t s = (int16_t)out_swizzle(1u << i, lv);
+    (bits[i].row >= 0 ? o.srow[bits[i].row] : o.scol[bits[i].col]) = s;
+  }
+  std::vector<int> pa, pc, pb, pn;
+  for (int j : rows) {
+    pa.push_back(am[j]);
+    pc.push_back(cm[j]);
+  }
+  if (!make_runs(pa, &idx.aM) || !make_runs(pc, &o.cM)) return;
+  pc.clear();
+  for (int j : cols) {
+    pc.push_back(cn[j]);
+    pn.push_back(j);
+    if (!gemm) pb.push_back(run_pos(idx.bN, j));
+  }
+  if (!make_runs(pc, &o.cN) || !make_runs(pn, &o.nmap) || (!gemm && !make_runs(pb, &idx.bN))) return;
+  if (gemm && !gemm_gather_ok(idx)) return;
+  if (gemm ? (half ? nM < 7 || idx.nK < 5 : op.gemm.K > kAccChain) : !skew_out_ok(P.opts.dtype, idx)) return;
+  F->idx = idx;
+  F->op = n_ops - 2;
+  F->ok = true;
 }
 
 int refold_leaves(PlanCore& P, std::string& err) {

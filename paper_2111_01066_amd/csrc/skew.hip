@@ -29,6 +29,7 @@
 #include "elem.h"
 #include "gather.h"
 #include "kernels.h"
+#include "outmap.h"
 
 namespace tnrcs {
 
@@ -245,6 +246,28 @@ __global__ __launch_bounds__(256, 2) void k_skew(const E* __restrict__ A, const 
   record_max_in(maxslot, mx, reinterpret_cast<float*>(bn));
 }
 
+// Walks the passes of a block in C's order: pass i of the block is pass
+// blockIdx + i gridDim (powers of two), so its offset in C moves by one XOR
+// with a prefix table (C's row bits need not keep their order).
+template <typename OM>
+struct OutPasses {
+  uint64_t at = 0;
+  __device__ __forceinline__ void init(const OM& om, uint64_t* pre, int tid, int nM) {
+    if constexpr (has_out<OM>) {
+      const int lg = __builtin_ctz(gridDim.x);
+      if (tid < nM - 7 - lg) {
+        uint64_t x = 0;
+        for (int j = 0; j <= tid; ++j) x ^= dep((uint64_t)kSkewPM << (lg + j), om.cM);
+        pre[tid] = x;
+      }
+      at = dep((uint64_t)blockIdx.x * kSkewPM, om.cM);
+    }
+  }
+  __device__ __forceinline__ void next(const uint64_t* pre, int64_t i) {  // from pass i to pass i + 1
+    at ^= pre[__builtin_ctzll((unsigned long long)(i + 1))];
+  }
+};
+
 // Steady-state form for B resident in LDS and K = KC * NCH <= 64: one loop
 // iteration is one pass of 128 rows, its NCH chunks unrolled, so the loads,
 // LDS stores, matrix products and C stores of a pass are straight-line code
@@ -256,10 +279,10 @@ __global__ __launch_bounds__(256, 2) void k_skew(const E* __restrict__ A, const 
 // STG: rows of at most 16 outputs (NT = 1): a pass's 128 x N outputs are one
 // contiguous range of C; they are staged in the (then idle) A chunk planes
 // and written in 16-byte runs instead of one 8- or 4-byte store per lane.
-template <int NT, int VEC, int KC, int NCH, int PD, int STG, typename E>
+template <int NT, int VEC, int KC, int NCH, int PD, int STG, typename E, typename OM>
 __global__ __launch_bounds__(256, 2) void k_skew_p(const E* __restrict__ A, const E* __restrict__ B,
                                                   E* __restrict__ C, const IndexOp op, const SkewMap mp,
-                                                  float* maxslot) {
+                                                  float* maxslot, const OM om) {
   constexpr int NP = 32 * NT, LDB = NP + 4, K = KC * NCH;
   constexpr int LPT = (kSkewPM * KC) / 256 / VEC;  // loads per thread per chunk
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -270,6 +293,18 @@ __global__ __launch_bounds__(256, 2) void k_skew_p(const E* __restrict__ A, cons
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = lane & 31, kh = lane >> 5;
   if (tid < 64) bn[tid] = tid < N ? dep((uint64_t)tid, op.bN) : 0;
+  // C in the caller's order: staging area, this lane's entries in it, offsets
+  OutPasses<OM> op_at;
+  __shared__ uint64_t pre_c[has_out<OM> ? 40 : 1];
+  op_at.init(om, pre_c, tid, op.nM);
+  int oat = 0;
+  uint64_t toff = 0, oj = 0;
+  if constexpr (has_out<OM>) {
+    oat = out_lane(om, c, kh) ^ (wave & 1 ? om.srow[5] : 0) ^ (wave >> 1 ? om.srow[6] : 0);
+    toff = out_thread<E>(om, tid);
+    if (NT > 1) oj = dep(32, om.cN);
+  }
+  E* Cs = reinterpret_cast<E*>(bn + 64);  // (has_out: room for 128 x min(N, 32) entries)
   uint64_t kA0[NCH];  // A offset of each chunk's first k (uniform)
 #pragma unroll
   for (int ch = 0; ch < NCH; ++ch) kA0[ch] = dep((uint64_t)ch * KC, op.aK);
@@ -375,6 +410,25 @@ __global__ __launch_bounds__(256, 2) void k_skew_p(const E* __restrict__ A, cons
             acc[2][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(ar[s2] + ai[s2], br[s2][j] + bi[s2][j], acc[2][j],
                                                              0, 0, 0);
           }
+      }
+      if constexpr (has_out<OM>) {
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+          if (j > 0) __syncthreads();  // the first block's runs have been read
+          if (c < N) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              const float cr = acc[0][j][r] - acc[1][j][r];
+              const float ci = acc[2][j][r] - acc[0][j][r] - acc[1][j][r];
+              mx = mag_max(mx, cr, ci);
+              Cs[oat ^ out_reg(om, r)] = from_f2<E>(cr * op.out_scale, ci * op.out_scale);
+            }
+          }
+          __syncthreads();
+          out_write<E, 12>(om, C, Cs, op_at.at | (j ? oj : 0), toff, tid);
+        }
+        if (pi + 1 < my_passes) op_at.next(pre_c, pi);
+        continue;
       }
       if constexpr (STG) {
         __syncthreads();  // every wave has multiplied the pass's last chunk
@@ -500,10 +554,10 @@ __device__ __forceinline__ void skew_store_half(H* s, const E (&v)[LPT][VEC], co
   }
 }
 
-template <int NT, int VEC, int MODE, int NCH, int PD, typename E>
+template <int NT, int VEC, int MODE, int NCH, int PD, typename E, typename OM>
 __global__ __launch_bounds__(256, 2) void k_skew_ph(const E* __restrict__ A, const E* __restrict__ B,
                                                    E* __restrict__ C, const IndexOp op, const SkewMap mp,
-                                                   float* maxslot) {
+                                                   float* maxslot, const OM om) {
   typedef typename SkewHalf<E>::H H;
   typedef typename SkewHalf<E>::V V;
   constexpr int KC = 16, NP = 32 * NT, K = KC * NCH;
@@ -520,6 +574,18 @@ __global__ __launch_bounds__(256, 2) void k_skew_ph(const E* __restrict__ A, con
   const int row0 = (1 << (MODE == kQuadKR ? mp.mb[1] : MODE == kQuadKK ? 0 : mp.mb[0])) * kSkewHS;
   const int row1 = MODE == kQuadRR ? (1 << mp.mb[1]) * kSkewHS : 0;
   if (tid < 64) bn[tid] = tid < N ? dep((uint64_t)tid, op.bN) : 0;
+  // C in the caller's order: staging area, this lane's entries in it, offsets
+  OutPasses<OM> op_at;
+  __shared__ uint64_t pre_c[has_out<OM> ? 40 : 1];
+  op_at.init(om, pre_c, tid, op.nM);
+  int oat = 0;
+  uint64_t toff = 0, oj = 0;
+  if constexpr (has_out<OM>) {
+    oat = out_lane(om, c, kh) ^ (wave & 1 ? om.srow[5] : 0) ^ (wave >> 1 ? om.srow[6] : 0);
+    toff = out_thread<E>(om, tid);
+    if (NT > 1) oj = dep(32, om.cN);
+  }
+  E* Cs = reinterpret_cast<E*>(bn + 64);  // (has_out: room for 128 x min(N, 32) entries)
   uint64_t kA0[NCH];
 #pragma unroll
   for (int ch = 0; ch < NCH; ++ch) kA0[ch] = dep((uint64_t)ch * KC, op.aK);
@@ -604,6 +670,25 @@ __global__ __launch_bounds__(256, 2) void k_skew_ph(const E* __restrict__ A, con
           acc[1][j] = SkewHalf<E>::mfma(ai, br, acc[1][j]);
         }
       }
+      if constexpr (has_out<OM>) {
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+          if (j > 0) __syncthreads();  // the first block's runs have been read
+          if (c < N) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              const float cr = acc[0][j][r];
+              const float ci = acc[1][j][r];
+              mx = mag_max(mx, cr, ci);
+              Cs[oat ^ out_reg(om, r)] = from_f2<E>(cr * op.out_scale, ci * op.out_scale);
+            }
+          }
+          __syncthreads();
+          out_write<E, 12>(om, C, Cs, op_at.at | (j ? oj : 0), toff, tid);
+        }
+        if (pi + 1 < my_passes) op_at.next(pre_c, pi);
+        continue;
+      }
 #pragma unroll
       for (int j = 0; j < NT; ++j) {
         const int col = 32 * j + c;
@@ -635,10 +720,10 @@ static size_t skew_ph_lds(int K, int np) { return 2 * kSkewPM * kSkewHS * 2 + 2 
 // pass the loads repeat the last pass's chunks (read, never used).
 constexpr int kSkewBS = 24;  // LDS row stride of a staged B chunk (entries)
 
-template <int NT, int VEC, int MODE, typename E>
+template <int NT, int VEC, int MODE, typename E, typename OM>
 __global__ __launch_bounds__(256, 2) void k_skew_phc(const E* __restrict__ A, const E* __restrict__ B,
                                                     E* __restrict__ C, const IndexOp op, const SkewMap mp,
-                                                    float* maxslot) {
+                                                    float* maxslot, const OM om) {
   typedef typename SkewHalf<E>::H H;
   typedef typename SkewHalf<E>::V V;
   constexpr int KC = 16, NP = 32 * NT;
@@ -655,6 +740,18 @@ __global__ __launch_bounds__(256, 2) void k_skew_phc(const E* __restrict__ A, co
   // LDS offsets of the row bits that a 16-byte load covers
   const int row0 = (1 << (MODE == kQuadKR ? mp.mb[1] : MODE == kQuadKK ? 0 : mp.mb[0])) * kSkewHS;
   const int row1 = MODE == kQuadRR ? (1 << mp.mb[1]) * kSkewHS : 0;
+  // C in the caller's order: staging area, this lane's entries in it, offsets
+  OutPasses<OM> op_at;
+  __shared__ uint64_t pre_c[has_out<OM> ? 40 : 1];
+  op_at.init(om, pre_c, tid, op.nM);
+  int oat = 0;
+  uint64_t toff = 0, oj = 0;
+  if constexpr (has_out<OM>) {
+    oat = out_lane(om, c, kh) ^ (wave & 1 ? om.srow[5] : 0) ^ (wave >> 1 ? om.srow[6] : 0);
+    toff = out_thread<E>(om, tid);
+    if (NT > 1) oj = dep(32, om.cN);
+  }
+  __shared__ __attribute__((aligned(16))) E Cs[has_out<OM> ? kSkewPM * 32 : 4];
   // prefix tables: chunk ch -> ch + 1 flips the chunk-index bits 0 .. ctz(ch + 1)
   if (tid < op.nK - 4) {
     uint64_t xa = 0, xb = 0;
@@ -768,6 +865,25 @@ __global__ __launch_bounds__(256, 2) void k_skew_phc(const E* __restrict__ A, co
         }
       }
     }
+      if constexpr (has_out<OM>) {
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+          if (j > 0) __syncthreads();  // the first block's runs have been read
+          if (c < N) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              const float cr = acc[0][j][r];
+              const float ci = acc[1][j][r];
+              mx = mag_max(mx, cr, ci);
+              Cs[oat ^ out_reg(om, r)] = from_f2<E>(cr * op.out_scale, ci * op.out_scale);
+            }
+          }
+          __syncthreads();
+          out_write<E, 12>(om, C, Cs, op_at.at | (j ? oj : 0), toff, tid);
+        }
+        if (pi + 1 < my_passes) op_at.next(pre_c, pi);
+        continue;
+      }
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
       const int col = 32 * j + c;
@@ -784,6 +900,18 @@ __global__ __launch_bounds__(256, 2) void k_skew_phc(const E* __restrict__ A, co
   }
   __syncthreads();
   record_max_in(maxslot, mx, red);
+}
+
+// Staged outputs of one block of 32 columns.
+static size_t skew_out_lds(int elem_bytes, int nN) { return (size_t)kSkewPM * (1 << std::min(nN, 5)) * elem_bytes; }
+
+bool skew_out_ok(int dtype, const IndexOp& op) {
+  if (!skew_ok(op)) return false;
+  const int eb = elem_bytes_of(dtype);
+  if (dtype != TN_DTYPE_C64 && op.nK >= 4) return true;
+  if (op.nK > 6) return false;
+  const size_t lds = skew_p_lds(1 << std::min(op.nK, 4), 1 << op.nK, op.nN <= 5 ? 32 : 64);
+  return lds + skew_out_lds(eb, op.nN) <= 64 * 1024 - 512;
 }
 
 bool skew_ok(const IndexOp& op) { return op.nN <= 6 && op.nK >= 1 && op.nK <= 10 && op.nM >= 7; }
@@ -876,43 +1004,51 @@ static hipError_t launch_skew_kc(const E* A, const E* B, E* C, const IndexOp& op
 
 template <int NT, int VEC, int KC, int NCH, typename E>
 static hipError_t launch_skew_pass(const E* A, const E* B, E* C, const IndexOp& op, const SkewMap& mp,
-                                   float* maxslot, hipStream_t s) {
+                                   float* maxslot, hipStream_t s, const OutMap* out) {
   constexpr int PD = NCH >= 4 ? 1 : 2;  // prefetch distance in passes: NCH * PD chunks
   const size_t lds = skew_p_lds(KC, KC * NCH, 32 * NT);
   const int64_t passes = ((int64_t)1 << op.nM) / kSkewPM;
   const dim3 g((unsigned)std::min<int64_t>(passes, 512));
+  if (out) {
+    hipLaunchKernelGGL((k_skew_p<NT, VEC, KC, NCH, PD, 0, E, OutMap>), g, dim3(256),
+                       lds + skew_out_lds((int)sizeof(E), op.nN), s, A, B, C, op, mp, maxslot, *out);
+    return hipGetLastError();
+  }
   // staged output rows: at most 16 per row, fitting the A chunk planes
   const bool stg = NT == 1 && op.nN <= 4 &&
                    (size_t)kSkewPM * ((size_t)1 << op.nN) * sizeof(E) <= (size_t)2 * KC * kSkewLDA * sizeof(float) &&
                    kSkewPM * ((int64_t)1 << op.nN) * (int64_t)sizeof(E) >= 16;
   if (stg)
-    hipLaunchKernelGGL((k_skew_p<NT, VEC, KC, NCH, PD, 1, E>), g, dim3(256), lds, s, A, B, C, op, mp, maxslot);
+    hipLaunchKernelGGL((k_skew_p<NT, VEC, KC, NCH, PD, 1, E, NoOut>), g, dim3(256), lds, s, A, B, C, op, mp, maxslot,
+                       NoOut{});
   else
-    hipLaunchKernelGGL((k_skew_p<NT, VEC, KC, NCH, PD, 0, E>), g, dim3(256), lds, s, A, B, C, op, mp, maxslot);
+    hipLaunchKernelGGL((k_skew_p<NT, VEC, KC, NCH, PD, 0, E, NoOut>), g, dim3(256), lds, s, A, B, C, op, mp, maxslot,
+                       NoOut{});
   return hipGetLastError();
 }
 
 template <int NT, int VEC, typename E>
 static hipError_t launch_skew_pk(const E* A, const E* B, E* C, const IndexOp& op, const SkewMap& mp, float* maxslot,
-                                 hipStream_t s) {
+                                 hipStream_t s, const OutMap* out) {
   switch (op.nK) {
     case 1:
-      if constexpr (VEC == 1) return launch_skew_pass<NT, VEC, 2, 1, E>(A, B, C, op, mp, maxslot, s);
+      if constexpr (VEC == 1) return launch_skew_pass<NT, VEC, 2, 1, E>(A, B, C, op, mp, maxslot, s, out);
       break;
     case 2:
-      if constexpr (VEC <= 2) return launch_skew_pass<NT, VEC, 4, 1, E>(A, B, C, op, mp, maxslot, s);
+      if constexpr (VEC <= 2) return launch_skew_pass<NT, VEC, 4, 1, E>(A, B, C, op, mp, maxslot, s, out);
       break;
-    case 3: return launch_skew_pass<NT, VEC, 8, 1, E>(A, B, C, op, mp, maxslot, s);
-    case 4: return launch_skew_pass<NT, VEC, 16, 1, E>(A, B, C, op, mp, maxslot, s);
-    case 5: return launch_skew_pass<NT, VEC, 16, 2, E>(A, B, C, op, mp, maxslot, s);
-    case 6: return launch_skew_pass<NT, VEC, 16, 4, E>(A, B, C, op, mp, maxslot, s);
+    case 3: return launch_skew_pass<NT, VEC, 8, 1, E>(A, B, C, op, mp, maxslot, s, out);
+    case 4: return launch_skew_pass<NT, VEC, 16, 1, E>(A, B, C, op, mp, maxslot, s, out);
+    case 5: return launch_skew_pass<NT, VEC, 16, 2, E>(A, B, C, op, mp, maxslot, s, out);
+    case 6: return launch_skew_pass<NT, VEC, 16, 4, E>(A, B, C, op, mp, maxslot, s, out);
     default: break;
   }
   return hipErrorInvalidValue;
 }
 
 template <int NT, typename E>
-static hipError_t launch_skew_t(const E* A, const E* B, E* C, const IndexOp& op, float* maxslot, hipStream_t s) {
+static hipError_t launch_skew_t(const E* A, const E* B, E* C, const IndexOp& op, float* maxslot, hipStream_t s,
+                                const OutMap* out) {
   constexpr int VEC = 16 / (int)sizeof(E);
   constexpr int LV = VEC == 4 ? 2 : 1;
   const int kcb = std::min(op.nK, 4);
@@ -925,12 +1061,12 @@ static hipError_t launch_skew_t(const E* A, const E* B, E* C, const IndexOp& op,
   // pass kernel: K <= 64 with B resident
   const bool pass = op.nK <= 6 && skew_p_lds(1 << kcb, 1 << op.nK, 32 * NT) <= 64 * 1024;
   if (vec) {
-    if (pass) return launch_skew_pk<NT, VEC, E>(A, B, C, op, mp, maxslot, s);
-    return launch_skew_kc<NT, VEC, E>(A, B, C, op, mp, maxslot, s);
+    if (pass) return launch_skew_pk<NT, VEC, E>(A, B, C, op, mp, maxslot, s, out);
+    return out ? hipErrorInvalidValue : launch_skew_kc<NT, VEC, E>(A, B, C, op, mp, maxslot, s);
   }
   if (!skew_map(op, kcb, 0, &mp)) return hipErrorInvalidValue;
-  if (pass) return launch_skew_pk<NT, 1, E>(A, B, C, op, mp, maxslot, s);
-  return launch_skew_kc<NT, 1, E>(A, B, C, op, mp, maxslot, s);
+  if (pass) return launch_skew_pk<NT, 1, E>(A, B, C, op, mp, maxslot, s, out);
+  return out ? hipErrorInvalidValue : launch_skew_kc<NT, 1, E>(A, B, C, op, mp, maxslot, s);
 }
 
 int quad_mode(SkewMap* mp, int lj) {
@@ -968,65 +1104,73 @@ int quad_mode(SkewMap* mp, int lj) {
 
 template <int NT, int VEC, int MODE, int NCH, typename E>
 static hipError_t launch_skew_half(const E* A, const E* B, E* C, const IndexOp& op, const SkewMap& mp,
-                                   float* maxslot, hipStream_t s) {
+                                   float* maxslot, hipStream_t s, const OutMap* out) {
   constexpr int PD = NCH >= 4 ? 1 : 2;
   const size_t lds = skew_ph_lds(16 * NCH, 32 * NT);
   const int64_t passes = ((int64_t)1 << op.nM) / kSkewPM;
   const dim3 g((unsigned)std::min<int64_t>(passes, 512));
-  hipLaunchKernelGGL((k_skew_ph<NT, VEC, MODE, NCH, PD, E>), g, dim3(256), lds, s, A, B, C, op, mp, maxslot);
+  if (out)
+    hipLaunchKernelGGL((k_skew_ph<NT, VEC, MODE, NCH, PD, E, OutMap>), g, dim3(256),
+                       lds + skew_out_lds((int)sizeof(E), op.nN), s, A, B, C, op, mp, maxslot, *out);
+  else
+    hipLaunchKernelGGL((k_skew_ph<NT, VEC, MODE, NCH, PD, E, NoOut>), g, dim3(256), lds, s, A, B, C, op, mp, maxslot,
+                       NoOut{});
   return hipGetLastError();
 }
 
 template <int NT, int VEC, int MODE, typename E>
 static hipError_t launch_skew_hn(const E* A, const E* B, E* C, const IndexOp& op, const SkewMap& mp, float* maxslot,
-                                 hipStream_t s) {
+                                 hipStream_t s, const OutMap* out) {
   switch (op.nK) {
-    case 4: return launch_skew_half<NT, VEC, MODE, 1, E>(A, B, C, op, mp, maxslot, s);
-    case 5: return launch_skew_half<NT, VEC, MODE, 2, E>(A, B, C, op, mp, maxslot, s);
-    case 6: return launch_skew_half<NT, VEC, MODE, 4, E>(A, B, C, op, mp, maxslot, s);
+    case 4: return launch_skew_half<NT, VEC, MODE, 1, E>(A, B, C, op, mp, maxslot, s, out);
+    case 5: return launch_skew_half<NT, VEC, MODE, 2, E>(A, B, C, op, mp, maxslot, s, out);
+    case 6: return launch_skew_half<NT, VEC, MODE, 4, E>(A, B, C, op, mp, maxslot, s, out);
     default: break;
   }
   // 128 <= K <= 2^10: B staged chunk by chunk
   const int64_t passes = ((int64_t)1 << op.nM) / kSkewPM;
   const dim3 g((unsigned)std::min<int64_t>(passes, 512));
-  hipLaunchKernelGGL((k_skew_phc<NT, VEC, MODE, E>), g, dim3(256), 0, s, A, B, C, op, mp, maxslot);
+  if (out)
+    hipLaunchKernelGGL((k_skew_phc<NT, VEC, MODE, E, OutMap>), g, dim3(256), 0, s, A, B, C, op, mp, maxslot, *out);
+  else
+    hipLaunchKernelGGL((k_skew_phc<NT, VEC, MODE, E, NoOut>), g, dim3(256), 0, s, A, B, C, op, mp, maxslot, NoOut{});
   return hipGetLastError();
 }
 
 // 16-bit storage with 16 <= K <= 2^10: the half-precision matrix cores
 template <int NT, typename E>
-static hipError_t launch_skew_h(const E* A, const E* B, E* C, const IndexOp& op, float* maxslot, hipStream_t s) {
+static hipError_t launch_skew_h(const E* A, const E* B, E* C, const IndexOp& op, float* maxslot, hipStream_t s, const OutMap* out) {
   SkewMap mp{};
   if (!skew_map(op, 4, 2, &mp)) return hipErrorInvalidValue;
   SkewMap q = mp;
   switch (quad_mode(&q, 1)) {
-    case kQuadKK: return launch_skew_hn<NT, 4, kQuadKK, E>(A, B, C, op, q, maxslot, s);
-    case kQuadKR: return launch_skew_hn<NT, 4, kQuadKR, E>(A, B, C, op, q, maxslot, s);
-    case kQuadRK: return launch_skew_hn<NT, 4, kQuadRK, E>(A, B, C, op, q, maxslot, s);
-    case kQuadRR: return launch_skew_hn<NT, 4, kQuadRR, E>(A, B, C, op, q, maxslot, s);
-    default: return launch_skew_hn<NT, 1, kQuadKK, E>(A, B, C, op, mp, maxslot, s);
+    case kQuadKK: return launch_skew_hn<NT, 4, kQuadKK, E>(A, B, C, op, q, maxslot, s, out);
+    case kQuadKR: return launch_skew_hn<NT, 4, kQuadKR, E>(A, B, C, op, q, maxslot, s, out);
+    case kQuadRK: return launch_skew_hn<NT, 4, kQuadRK, E>(A, B, C, op, q, maxslot, s, out);
+    case kQuadRR: return launch_skew_hn<NT, 4, kQuadRR, E>(A, B, C, op, q, maxslot, s, out);
+    default: return launch_skew_hn<NT, 1, kQuadKK, E>(A, B, C, op, mp, maxslot, s, out);
   }
 }
 
 template <typename E>
-static hipError_t launch_skew_e(const E* A, const E* B, E* C, const IndexOp& op, float* maxslot, hipStream_t s) {
+static hipError_t launch_skew_e(const E* A, const E* B, E* C, const IndexOp& op, float* maxslot, hipStream_t s, const OutMap* out) {
   if constexpr (sizeof(E) == 4) {
     if (op.nK >= 4) {
-      if (op.nN <= 5) return launch_skew_h<1, E>(A, B, C, op, maxslot, s);
-      return launch_skew_h<2, E>(A, B, C, op, maxslot, s);
+      if (op.nN <= 5) return launch_skew_h<1, E>(A, B, C, op, maxslot, s, out);
+      return launch_skew_h<2, E>(A, B, C, op, maxslot, s, out);
     }
   }
-  if (op.nN <= 5) return launch_skew_t<1, E>(A, B, C, op, maxslot, s);
-  return launch_skew_t<2, E>(A, B, C, op, maxslot, s);
+  if (op.nN <= 5) return launch_skew_t<1, E>(A, B, C, op, maxslot, s, out);
+  return launch_skew_t<2, E>(A, B, C, op, maxslot, s, out);
 }
 
 hipError_t launch_skew(int dtype, const void* A, const void* B, void* C, const IndexOp& op, float* maxslot,
-                       hipStream_t s) {
+                       hipStream_t s, const OutMap* out) {
   if (!skew_ok(op)) return hipErrorInvalidValue;
-  if (dtype == TN_DTYPE_F16S) return launch_skew_e<cf16>((const cf16*)A, (const cf16*)B, (cf16*)C, op, maxslot, s);
+  if (dtype == TN_DTYPE_F16S) return launch_skew_e<cf16>((const cf16*)A, (const cf16*)B, (cf16*)C, op, maxslot, s, out);
   if (dtype == TN_DTYPE_BF16S)
-    return launch_skew_e<cbf16>((const cbf16*)A, (const cbf16*)B, (cbf16*)C, op, maxslot, s);
-  return launch_skew_e<float2>((const float2*)A, (const float2*)B, (float2*)C, op, maxslot, s);
+    return launch_skew_e<cbf16>((const cbf16*)A, (const cbf16*)B, (cbf16*)C, op, maxslot, s, out);
+  return launch_skew_e<float2>((const float2*)A, (const float2*)B, (float2*)C, op, maxslot, s, out);
 }
 
 }  // namespace tnrcs
