@@ -21,6 +21,7 @@ constexpr int kSkinnyMaxLog2 = 11;  // the skewed kernel keeps 2^(nK+nN) <= 2^11
 // (u = 2^-24), about 6e-6 for n = 2^17, so long contractions are summed in
 // runs of this length (about 8e-7 at n = 2^17).
 constexpr int kAccChain = 2048;
+constexpr int kSplitMinK = 256;  // terms per slab of a split GEMM sum
 
 // Bit-deposit map: value bit (src + i) goes to target bit (dst + i) for
 // i < len, for each run.  Built from "value bit j -> target position pos[j]".

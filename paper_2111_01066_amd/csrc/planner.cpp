@@ -848,6 +848,11 @@ int build_plan(PlanCore& P, std::string& err) {
         while (tiles * sp < 2048 && ((int64_t)1 << nK) / (sp * 2) >= 1024 && sp < 64 &&
                ((int64_t)sp * 2 << (nM + nN)) <= ((int64_t)1 << 28))
           sp *= 2;
+        // and down to slabs of kSplitMinK terms while there are fewer than
+        // two workgroups per CU (FP16, 256 x 128 outputs over 2^11 terms: 43
+        // us in 2 slabs, 21 in 8; complex64, 4096 x 256 over 2^12: 276 us in
+        // 4, 249 in 8)
+        while (tiles * sp < 512 && ((int64_t)1 << nK) / (sp * 2) >= kSplitMinK && sp < 64) sp *= 2;
         // with tuning, room for every split the tuner may try: slabs of at
         // least 256 along K, at most 64 slabs, workspace <= 2^28 entries,
         // and only while the output has fewer than 8192 64x64 tiles
