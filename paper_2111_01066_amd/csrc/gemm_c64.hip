@@ -143,10 +143,17 @@ struct GatherA {
 };
 
 // 128x128 workgroup tile, four waves of 64x64 (2x2 blocks of 32x32 MFMA
-// tiles), K staged through LDS 16 at a time; the next K tile is loaded into
-// registers while the current one is multiplied.  Planar LDS: re, im; the
-// 3M operand sums re+im are formed in registers after the LDS reads, which
+// tiles, 64 rows and columns apart), K staged through LDS 16 at a time; the
+// next K tile is loaded into registers while the current one is multiplied.
+// The 3M operand sums re+im are formed in registers after the LDS reads, which
 // keeps the kernel within 256 registers per lane (two waves per SIMD).
+// A vector instruction does not overlap an FP32 product of the same SIMD: one
+// between two products costs 12 cycles, each further one 4 (a product takes
+// 64).  So LDS holds (re, im) pairs at strides that fit the read
+// instruction's two offsets: no address arithmetic in the K loop, and half
+// the LDS instructions of separate planes (8192 x 8192 x 2048 in 3M 178 -> 186
+// complex TFLOP/s, 2^18 x 128 x 256 161 -> 167; the rank-26 x rank-26 pair
+// 3.28 -> 3.16 ms, with A read in place).
 // blockIdx.z selects a batch entry or a split-K slab through the strides sA,
 // sB, sC (GA = 0 only).
 template <int FORM, int GA, typename OM>
@@ -155,11 +162,14 @@ __global__ __launch_bounds__(256, 2) void k_cgemm128(const float2* __restrict__ 
                                                  int64_t sA, int64_t sB, int64_t sC, int64_t Mt, int64_t Nt,
                                                  int chunk, const GatherA g, const OM om) {
   constexpr int P = (FORM == TN_GEMM_3M) ? 3 : 2;
-  constexpr int BM = 128, BN = 128, BK = 16, LD = BM + 2;
+  constexpr int BM = 128, BN = 128, BK = 16, LD = 128;
   constexpr int LPT = 4;  // gathered A: 16-byte loads per thread per chunk
-  __shared__ __attribute__((aligned(16))) float AB[2][2][BK][LD];
-  float (*As)[BK][LD] = AB[0];
-  float (*Bs)[BK][LD] = AB[1];
+  // entry (k, row) of A and B at k * LD + (row ^ swz(k)): the two k halves of
+  // a row that neighbouring threads store go to different banks
+  __shared__ __attribute__((aligned(16))) float2 AB[2][BK * LD];
+  float2* As = AB[0];
+  float2* Bs = AB[1];
+  auto swz = [](int k) { return (k & 8) << 1; };
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int64_t tm, tn, z;
   xcd_tile(blockIdx.x, Mt, Nt, gridDim.x, tm, tn, z);
@@ -167,7 +177,7 @@ __global__ __launch_bounds__(256, 2) void k_cgemm128(const float2* __restrict__ 
   A += z * sA;
   B += z * sB;
   C += z * sC;
-  const int wm = (wave & 1) * 64, wn = (wave >> 1) * 64;
+  const int wm = (wave & 1) * 32, wn = (wave >> 1) * 32;  // and 64 further on
   floatx16 acc[P][2][2];
 #pragma unroll
   for (int p = 0; p < P; ++p)
@@ -176,34 +186,38 @@ __global__ __launch_bounds__(256, 2) void k_cgemm128(const float2* __restrict__ 
 #pragma unroll
       for (int j = 0; j < 2; ++j) acc[p][i][j] = floatx16{};
   const int lrow = tid >> 1, lk = (tid & 1) * 8;
+  const int slot0 = lk * LD + (lrow ^ swz(lk));  // entries (lk + q, lrow) at slot0 + q * LD
   const float2* Ap = A + (bm + lrow) * K + lk;
   int64_t brow_b = bn + lrow;
   if constexpr (has_out<OM>) brow_b = (int64_t)dep((uint64_t)brow_b, om.nmap);
   const float2* Bp = B + brow_b * K + lk;
   float4 ra[4], rb[4];
-  // gathered A: this thread's two entries per load (offset of the first
-  // from the chunk's first entry; LDS indices k * LD + m of both, packed in
-  // 16 bits each), the tile's row offset and the chunk's K offset
-  uint32_t eoff[GA ? LPT : 1], eidx[GA ? LPT : 1];
+  // gathered A: a thread's entries are (j * 256 + tid) * 2 and the next one.
+  // Offsets and LDS entries are sums (XORs) over the bits of that number, so
+  // only tid's part is held per lane; j's and the odd entry's are uniform
+  uint32_t eoff = 0, eidx = 0, uidx[GA ? LPT : 1], uodd = 0;
+  uint64_t uoff[GA ? LPT : 1];
   uint64_t abase = 0, kofs = 0;
   float4 rg[GA ? LPT : 1];
   if constexpr (GA != 0) {
+    auto entry = [&](int e, uint64_t& off) {
+      int m, k;
+      skew_split(g.mp, e, off, m, k);
+      return (uint32_t)(k * LD + (m ^ swz(k)));
+    };
+    uint64_t off;
+    uodd = entry(1, off);
+    eidx = entry(tid * 2, off);
+    eoff = (uint32_t)off;
 #pragma unroll
-    for (int j = 0; j < LPT; ++j) {
-      uint64_t off, off1;
-      int m0, k0, m1, k1;
-      skew_split(g.mp, (j * 256 + tid) * 2, off, m0, k0);
-      skew_split(g.mp, (j * 256 + tid) * 2 + 1, off1, m1, k1);
-      eoff[j] = (uint32_t)off;
-      eidx[j] = (uint32_t)(k0 * LD + m0) | ((uint32_t)(k1 * LD + m1) << 16);
-    }
+    for (int j = 0; j < LPT; ++j) uidx[j] = entry(j * 512, uoff[j]);
     abase = dep_u<12>((uint64_t)bm, g.aM);
   }
   auto load_a = [&]() {
     if constexpr (GA != 0) {
       const float2* base = A + (abase + kofs);
 #pragma unroll
-      for (int j = 0; j < LPT; ++j) rg[j] = *reinterpret_cast<const float4*>(base + eoff[j]);
+      for (int j = 0; j < LPT; ++j) rg[j] = *reinterpret_cast<const float4*>(base + uoff[j] + eoff);
     }
   };
 #pragma unroll
@@ -238,7 +252,7 @@ __global__ __launch_bounds__(256, 2) void k_cgemm128(const float2* __restrict__ 
             v.x = acc[0][i][j][r];
             v.y = acc[1][i][j][r];
           }
-          float2* p = Cw + (32 * i + 8 * (r >> 2) + (r & 3)) * ld + 32 * j;
+          float2* p = Cw + (64 * i + 8 * (r >> 2) + (r & 3)) * ld + 64 * j;
           if constexpr (ADD) {
             const float2 o = *p;
             v.x += o.x;
@@ -251,6 +265,11 @@ __global__ __launch_bounds__(256, 2) void k_cgemm128(const float2* __restrict__ 
         __builtin_amdgcn_sched_barrier(0);  // one 32x32 block's loads in flight at a time
       }
   };
+  // this lane's operands: rows wm + c and wm + 64 + c at k = kk + kh
+  const float2* a_lo = As + kh * LD + wm + c;
+  const float2* a_hi = As + kh * LD + ((wm + c) ^ 16);
+  const float2* b_lo = Bs + kh * LD + wn + c;
+  const float2* b_hi = Bs + kh * LD + ((wn + c) ^ 16);
   bool first = true;
   int it = 0;
   for (int64_t k0 = 0; k0 < k_len; k0 += BK, ++it) {
@@ -258,26 +277,19 @@ __global__ __launch_bounds__(256, 2) void k_cgemm128(const float2* __restrict__ 
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       if constexpr (GA == 0) {
-        As[0][lk + 2 * j][lrow] = ra[j].x;
-        As[1][lk + 2 * j][lrow] = ra[j].y;
-        As[0][lk + 2 * j + 1][lrow] = ra[j].z;
-        As[1][lk + 2 * j + 1][lrow] = ra[j].w;
+        As[slot0 + 2 * j * LD] = make_float2(ra[j].x, ra[j].y);
+        As[slot0 + (2 * j + 1) * LD] = make_float2(ra[j].z, ra[j].w);
       }
-      Bs[0][lk + 2 * j][lrow] = rb[j].x;
-      Bs[1][lk + 2 * j][lrow] = rb[j].y;
-      Bs[0][lk + 2 * j + 1][lrow] = rb[j].z;
-      Bs[1][lk + 2 * j + 1][lrow] = rb[j].w;
+      Bs[slot0 + 2 * j * LD] = make_float2(rb[j].x, rb[j].y);
+      Bs[slot0 + (2 * j + 1) * LD] = make_float2(rb[j].z, rb[j].w);
     }
     if constexpr (GA != 0) {
-      float* a0 = &As[0][0][0];
-      float* a1 = &As[1][0][0];
+      uint32_t e = eidx;
+      asm volatile("" : "+v"(e));  // the XORs stay here: no registers for them across the K loop
 #pragma unroll
       for (int j = 0; j < LPT; ++j) {
-        const int i0 = (int)(eidx[j] & 0xffffu), i1 = (int)(eidx[j] >> 16);
-        a0[i0] = rg[j].x;
-        a1[i0] = rg[j].y;
-        a0[i1] = rg[j].z;
-        a1[i1] = rg[j].w;
+        As[e ^ uidx[j]] = make_float2(rg[j].x, rg[j].y);
+        As[e ^ uidx[j] ^ uodd] = make_float2(rg[j].z, rg[j].w);
       }
     }
     if (chunk > 0 && it > 0 && it % chunk == 0) {
@@ -301,15 +313,15 @@ __global__ __launch_bounds__(256, 2) void k_cgemm128(const float2* __restrict__ 
     }
 #pragma unroll
     for (int kk = 0; kk < BK; kk += 2) {
-      const int kr = kk + kh;
       float a[P][2], b[P][2];
 #pragma unroll
-      for (int p = 0; p < 2; ++p)
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          a[p][i] = As[p][kr][wm + 32 * i + c];
-          b[p][i] = Bs[p][kr][wn + 32 * i + c];
-        }
+      for (int i = 0; i < 2; ++i) {
+        const float2 x = (kk < 8 ? a_lo : a_hi)[kk * LD + 64 * i], y = (kk < 8 ? b_lo : b_hi)[kk * LD + 64 * i];
+        a[0][i] = x.x;
+        a[1][i] = x.y;
+        b[0][i] = y.x;
+        b[1][i] = y.y;
+      }
       if (P == 3)  // 3M operand sums, formed in FP32 from the staged re/im
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
@@ -337,11 +349,11 @@ __global__ __launch_bounds__(256, 2) void k_cgemm128(const float2* __restrict__ 
   if constexpr (has_out<OM>) {
     // (sums of at most one chunk: nothing has been stored yet.)  Blocks (i, j)
     // of all four waves: one sub-tile in C's order at a time
-    float2* Cs = reinterpret_cast<float2*>(&AB[0][0][0][0]);
-    const int at = out_lane(om, c, kh) ^ (wave & 1 ? om.srow[6] : 0) ^ (wave >> 1 ? om.scol[6] : 0);
+    float2* Cs = AB[0];
+    const int at = out_lane(om, c, kh) ^ (wave & 1 ? om.srow[5] : 0) ^ (wave >> 1 ? om.scol[5] : 0);
     const uint64_t tile = dep_u<12>((uint64_t)bm, om.cM) | dep_u<12>((uint64_t)bn, om.cN);
     const uint64_t toff = out_thread<float2>(om, tid);
-    const uint64_t oi = dep_u<12>(32, om.cM), oj = dep_u<12>(32, om.cN);
+    const uint64_t oi = dep_u<12>(64, om.cM), oj = dep_u<12>(64, om.cN);
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll

@@ -1133,8 +1133,8 @@ void plan_fused_out(const PlanCore& P, FusedOut* F) {
   for (int j = 0; j < nN; ++j) cn[j] = cpos[j];
   // The 7 row bits of a tile: the bit that ends the shorter of the two runs of
   // consecutive positions, A's and C's, until there are 7; the least wanted one is
-  // bit 5 (the complex64 GEMM stages the two 32-row blocks of a wave's rows
-  // one after the other).  The other row bits follow in A's order.
+  // bit 6 (the complex64 GEMM stages its two 64-row halves one after the
+  // other).  The other row bits follow in A's order.
   std::vector<int> tile;
   auto take = [&](int j) {
     if ((int)tile.size() < 7 && std::find(tile.begin(), tile.end(), j) == tile.end()) tile.push_back(j);
@@ -1186,27 +1186,26 @@ void plan_fused_out(const PlanCore& P, FusedOut* F) {
   std::sort(rows.begin(), rows.end(), [&](int x, int y) { return am[x] < am[y]; });
   if (gemm) {
     rows.erase(std::find(rows.begin(), rows.end(), tile.back()));
-    rows.insert(rows.begin() + 5, tile.back());
+    rows.push_back(tile.back());
   }
   for (int j : by_a)
     if (std::find(tile.begin(), tile.end(), j) == tile.end()) rows.push_back(j);
-  // columns: C's lowest positions first; bit 5 (a GEMM's 64-column halves, a
-  // skewed step's second block of 32) is the least wanted of the tile's
+  // columns: C's lowest positions first; a GEMM's 64-column halves (bit 6) and
+  // a skewed step's blocks of 32 (bit 5) are told apart by the highest
   std::vector<int> cols(nN);
   for (int j = 0; j < nN; ++j) cols[j] = j;
   std::sort(cols.begin(), cols.end(), [&](int x, int y) { return cn[x] < cn[y]; });
-  if (gemm && nN >= 7) std::swap(cols[5], cols[6]);
   OutMap& o = F->out;
   // sub-tile bits: all tile bits but, where the tile is staged in parts, row
-  // bit 5 (GEMM) and column bit 5
+  // and column bit 6 (GEMM) or column bit 5 (skewed)
   struct Bit {
     int c, row, col;
   };
   std::vector<Bit> bits;
   for (int b = 0; b < 7; ++b)
-    if (whole || !gemm || b != 5) bits.push_back({cm[rows[b]], b, -1});
+    if (whole || !gemm || b != 6) bits.push_back({cm[rows[b]], b, -1});
   for (int b = 0; b < std::min(nN, 7); ++b)
-    if (whole || b != 5) bits.push_back({cn[cols[b]], -1, b});
+    if (whole || b != (gemm ? 6 : 5)) bits.push_back({cn[cols[b]], -1, b});
   if ((int)bits.size() > kOutMaxBits) return;
   std::sort(bits.begin(), bits.end(), [](const Bit& x, const Bit& y) { return x.c < y.c; });
   // 16-byte stores: the sub-tile's lowest bits are C's (the bits left out of
