@@ -20,18 +20,26 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 // (four real products).  3M form: T1 = ArBr, T2 = AiBi,
 // T3 = (Ar+Ai)(Br+Bi); Cr = T1 - T2, Ci = T3 - T1 - T2 (three products).
 // Workgroup tile 64x64, four waves of 32x32, K staged through LDS in steps of
-// 16 with re/im split into planar arrays.
+// 16 as (re, im) pairs; the next stage is loaded into registers while the
+// current one is multiplied.  With few workgroups per CU a stage's load
+// latency bounds it, with many the FP32 products: with planes in LDS and each
+// stage loaded where it was used, 3 x 1984 x 1088 x 1200 took 470 us (now 428),
+// 192 x 320 x 2048 in 4 slabs 52 (37), 64 x 64 x 1024 80 (64).  Four waves per
+// SIMD: five spill and are no faster.
 
 constexpr int GBM = 64, GBN = 64, GBK = 16;
 
 // blockIdx.z selects a batch entry or a split-K slab through the strides sA,
 // sB, sC; each sums k_len terms of rows that are K long.
 template <int FORM>
-__global__ __launch_bounds__(256) void k_cgemm(const float2* __restrict__ A, const float2* __restrict__ B,
+__global__ __launch_bounds__(256, 4) void k_cgemm(const float2* __restrict__ A, const float2* __restrict__ B,
                                               float2* __restrict__ C, int64_t N, int64_t K, int64_t k_len,
                                               int64_t sA, int64_t sB, int64_t sC, int chunk) {
-  __shared__ float As[2][GBK][GBM + 4];
-  __shared__ float Bs[2][GBK][GBN + 4];
+  constexpr int LD = GBM;
+  // entry (k, row) of A and B at k * LD + (row ^ swz(k)): the four k quarters
+  // of a row that neighbouring threads store go to different banks
+  __shared__ __attribute__((aligned(16))) float2 As[GBK * LD], Bs[GBK * LD];
+  auto swz = [](int k) { return (k & 12) << 1; };
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int64_t bm = (int64_t)blockIdx.x * GBM, bn = (int64_t)blockIdx.y * GBN;
@@ -44,13 +52,24 @@ __global__ __launch_bounds__(256) void k_cgemm(const float2* __restrict__ A, con
   const int lrow = tid >> 2, lk = (tid & 3) * 4;
   const float2* Ap = A + (bm + lrow) * K + lk;
   const float2* Bp = B + (bn + lrow) * K + lk;
-  const int j = lane & 31;
+  const int slot0 = lk * LD + (lrow ^ swz(lk));  // entries (lk + q, lrow) at slot0 + q * LD
+  float4 ra[2], rb[2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    ra[q] = *reinterpret_cast<const float4*>(Ap + 2 * q);
+    rb[q] = *reinterpret_cast<const float4*>(Bp + 2 * q);
+  }
+  const int j = lane & 31, kh = lane >> 5;
   // adds (ADD false: stores) the running FP32 sums to C and restarts them
   auto flush = [&](auto add) {
     constexpr bool ADD = decltype(add)::value;
+    // the row stride is made opaque here so that the compiler does not keep
+    // the 16 output addresses live across the K loop
+    int64_t ld = N;
+    asm volatile("" : "+s"(ld));
+    float2* Cw = C + (bm + wm + 4 * kh) * ld + bn + wn + j;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const int i = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
       float2 v;
       if (FORM == TN_GEMM_3M) {
         v.x = c0[r] - c1[r];
@@ -59,7 +78,7 @@ __global__ __launch_bounds__(256) void k_cgemm(const float2* __restrict__ A, con
         v.x = c0[r];
         v.y = c1[r];
       }
-      float2* p = C + (bm + wm + i) * N + bn + wn + j;
+      float2* p = Cw + (8 * (r >> 2) + (r & 3)) * ld;
       if constexpr (ADD) {
         const float2 o = *p;
         v.x += o.x;
@@ -71,9 +90,24 @@ __global__ __launch_bounds__(256) void k_cgemm(const float2* __restrict__ A, con
     c1 = floatx16{};
     c2 = floatx16{};
   };
+  // this lane's operands: rows wm + j and wn + j at k = 4 q + kh and 4 q + 2 + kh
+  const float2 *Al[4], *Bl[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    Al[q] = As + (4 * q + kh) * LD + ((wm + j) ^ (8 * q));
+    Bl[q] = Bs + (4 * q + kh) * LD + ((wn + j) ^ (8 * q));
+  }
   bool first = true;
   int it = 0;
   for (int64_t k0 = 0; k0 < k_len; k0 += GBK, ++it) {
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      As[slot0 + 2 * q * LD] = make_float2(ra[q].x, ra[q].y);
+      As[slot0 + (2 * q + 1) * LD] = make_float2(ra[q].z, ra[q].w);
+      Bs[slot0 + 2 * q * LD] = make_float2(rb[q].x, rb[q].y);
+      Bs[slot0 + (2 * q + 1) * LD] = make_float2(rb[q].z, rb[q].w);
+    }
     if (chunk > 0 && it > 0 && it % chunk == 0) {
       if (first)
         flush(std::false_type{});
@@ -81,34 +115,18 @@ __global__ __launch_bounds__(256) void k_cgemm(const float2* __restrict__ A, con
         flush(std::true_type{});
       first = false;
     }
-    const float4 a01 = *reinterpret_cast<const float4*>(Ap + k0);
-    const float4 a23 = *reinterpret_cast<const float4*>(Ap + k0 + 2);
-    const float4 b01 = *reinterpret_cast<const float4*>(Bp + k0);
-    const float4 b23 = *reinterpret_cast<const float4*>(Bp + k0 + 2);
-    As[0][lk + 0][lrow] = a01.x;
-    As[1][lk + 0][lrow] = a01.y;
-    As[0][lk + 1][lrow] = a01.z;
-    As[1][lk + 1][lrow] = a01.w;
-    As[0][lk + 2][lrow] = a23.x;
-    As[1][lk + 2][lrow] = a23.y;
-    As[0][lk + 3][lrow] = a23.z;
-    As[1][lk + 3][lrow] = a23.w;
-    Bs[0][lk + 0][lrow] = b01.x;
-    Bs[1][lk + 0][lrow] = b01.y;
-    Bs[0][lk + 1][lrow] = b01.z;
-    Bs[1][lk + 1][lrow] = b01.w;
-    Bs[0][lk + 2][lrow] = b23.x;
-    Bs[1][lk + 2][lrow] = b23.y;
-    Bs[0][lk + 3][lrow] = b23.z;
-    Bs[1][lk + 3][lrow] = b23.w;
     __syncthreads();
+    if (k0 + GBK < k_len) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        ra[q] = *reinterpret_cast<const float4*>(Ap + k0 + GBK + 2 * q);
+        rb[q] = *reinterpret_cast<const float4*>(Bp + k0 + GBK + 2 * q);
+      }
+    }
 #pragma unroll
     for (int kk = 0; kk < GBK; kk += 2) {
-      const int kr = kk + (lane >> 5);
-      const float ar = As[0][kr][wm + (lane & 31)];
-      const float ai = As[1][kr][wm + (lane & 31)];
-      const float br = Bs[0][kr][wn + (lane & 31)];
-      const float bi = Bs[1][kr][wn + (lane & 31)];
+      const float2 a = Al[kk >> 2][(kk & 2) * LD], b = Bl[kk >> 2][(kk & 2) * LD];
+      const float ar = a.x, ai = a.y, br = b.x, bi = b.y;
       if (FORM == TN_GEMM_3M) {
         c0 = __builtin_amdgcn_mfma_f32_32x32x2f32(ar, br, c0, 0, 0, 0);
         c1 = __builtin_amdgcn_mfma_f32_32x32x2f32(ai, bi, c1, 0, 0, 0);
@@ -120,7 +138,6 @@ __global__ __launch_bounds__(256) void k_cgemm(const float2* __restrict__ A, con
         c1 = __builtin_amdgcn_mfma_f32_32x32x2f32(ai, br, c1, 0, 0, 0);
       }
     }
-    __syncthreads();
   }
   if (first)
     flush(std::false_type{});
