@@ -302,10 +302,13 @@ static int launch_op(tn_plan_s* p, const Op& op, hipStream_t s) {
       break;
     case kOpGemm:
       if (op.gemm.gather_a && dt == TN_DTYPE_C64)
-        HIP_TRY(launch_gemm_c64_ga((const float2*)a, (const float2*)b, (float2*)c, op.idx, op.gemm.form, s),
+        HIP_TRY(launch_gemm_c64_ga((const float2*)a, (const float2*)b, (float2*)c, op.idx, op.gemm.form, s,
+                                   op.gemm.split_k > 1 ? w : nullptr, op.gemm.split_k),
                 "gemm kernel (A in place)");
       else if (op.gemm.gather_a)
-        HIP_TRY(launch_gemm_half_ga(dt, a, b, c, op.idx, op.gemm.out_scale, slot, s), "half gemm kernel (A in place)");
+        HIP_TRY(launch_gemm_half_ga(dt, a, b, c, op.idx, op.gemm.out_scale, slot, s,
+                                    op.gemm.split_k > 1 ? w : nullptr, op.gemm.split_k),
+                "half gemm kernel (A in place)");
       else if (dt == TN_DTYPE_C64)
         HIP_TRY(launch_gemm_c64((const float2*)a, (const float2*)b, (float2*)c, op.gemm.M, op.gemm.N, op.gemm.K, 1,
                                 op.gemm.form, s, op.gemm.split_k > 1 ? w : nullptr, op.gemm.split_k, op.gemm.tile),
@@ -346,10 +349,10 @@ static int launch_fused(tn_plan_s* p, hipStream_t s) {
   if (op.kind == kOpSkew)
     HIP_TRY(launch_skew(dt, a, b, c, idx, slot, s, &F.out), "skewed contraction kernel (C in place)");
   else if (dt == TN_DTYPE_C64)
-    HIP_TRY(launch_gemm_c64_ga((const float2*)a, (const float2*)b, (float2*)c, idx, op.gemm.form, s, &F.out),
+    HIP_TRY(launch_gemm_c64_ga((const float2*)a, (const float2*)b, (float2*)c, idx, op.gemm.form, s, nullptr, 1, &F.out),
             "gemm kernel (C in place)");
   else
-    HIP_TRY(launch_gemm_half_ga(dt, a, b, c, idx, op.gemm.out_scale, slot, s, &F.out),
+    HIP_TRY(launch_gemm_half_ga(dt, a, b, c, idx, op.gemm.out_scale, slot, s, nullptr, 1, &F.out),
             "half gemm kernel (C in place)");
   return TN_OK;
 }

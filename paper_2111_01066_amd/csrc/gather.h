@@ -29,6 +29,31 @@ struct SkewMap {
   int8_t hm[2];
 };
 
+// The slab bits of a K split: bit i of the slab's number at position pos[i]
+// of A (the uppermost k bits; n of them).
+struct SlabMap {
+  int32_t n = 0;
+  int8_t pos[6] = {0, 0, 0, 0, 0, 0};
+};
+
+__device__ __forceinline__ uint64_t slab_offset(const SlabMap& s, int64_t z) {
+  uint64_t o = 0;
+#pragma unroll
+  for (int i = 0; i < 6; ++i)
+    if (i < s.n) o |= (uint64_t)((z >> i) & 1) << s.pos[i];
+  return o;
+}
+
+// splits (a power of two up to 64) slabs of idx's sum, each a whole number of
+// 2^stage_bits terms
+inline bool slab_map(const IndexOp& idx, int splits, int stage_bits, SlabMap* s) {
+  *s = SlabMap{};
+  while ((1 << s->n) < splits) ++s->n;
+  if (splits < 1 || (1 << s->n) != splits || s->n > 6 || idx.nK - s->n < stage_bits) return false;
+  for (int i = 0; i < s->n; ++i) s->pos[i] = (int8_t)run_pos(idx.aK, idx.nK - s->n + i);
+  return true;
+}
+
 __device__ __forceinline__ int skew_h(const SkewMap& mp, int m, int k) {
   int h = 0;
 #pragma unroll

@@ -157,6 +157,7 @@ struct GatherA {
   SkewMap mp;
   Runs aM;
   uint64_t maskK = 0, incK = 0;
+  SlabMap slab{};
 };
 
 // 128x128 workgroup tile, four waves of 64x64 (2x2 blocks of 32x32 MFMA
@@ -171,8 +172,8 @@ struct GatherA {
 // the LDS instructions of separate planes (8192 x 8192 x 2048 in 3M 178 -> 186
 // complex TFLOP/s, 2^18 x 128 x 256 161 -> 167; the rank-26 x rank-26 pair
 // 3.28 -> 3.16 ms, with A read in place).
-// blockIdx.z selects a batch entry or a split-K slab through the strides sA,
-// sB, sC (GA = 0 only).
+// z selects a batch entry or a split-K slab through the strides sA, sB, sC
+// (GA: slabs only, A's through g.slab).
 template <int FORM, int GA, typename OM>
 __global__ __launch_bounds__(256, 2) void k_cgemm128(const float2* __restrict__ A, const float2* __restrict__ B,
                                                  float2* __restrict__ C, int64_t N, int64_t K, int64_t k_len,
@@ -229,6 +230,7 @@ __global__ __launch_bounds__(256, 2) void k_cgemm128(const float2* __restrict__ 
 #pragma unroll
     for (int j = 0; j < LPT; ++j) uidx[j] = entry(j * 512, uoff[j]);
     abase = dep_u<12>((uint64_t)bm, g.aM);
+    kofs = slab_offset(g.slab, z);
   }
   auto load_a = [&]() {
     if constexpr (GA != 0) {
@@ -489,19 +491,30 @@ static uint64_t dep_host(uint64_t x, const Runs& r) {
 }
 
 hipError_t launch_gemm_c64_ga(const float2* A, const float2* B, float2* C, const IndexOp& idx, int form,
-                              hipStream_t s, const OutMap* out) {
-  if (!gemm_gather_ok(idx)) return hipErrorInvalidValue;
+                              hipStream_t s, float2* work, int splits, const OutMap* out) {
+  if (!gemm_gather_ok(idx) || (splits > 1 && (!work || out))) return hipErrorInvalidValue;
   const int64_t M = (int64_t)1 << idx.nM, N = (int64_t)1 << idx.nN, K = (int64_t)1 << idx.nK;
   GatherA g{};
   skew_map(idx, 4, 0, &g.mp);
   g.aM = idx.aM;
   g.maskK = dep_host((uint64_t)(K - 1) & ~(uint64_t)15, idx.aK);
   g.incK = K > 16 ? dep_host(16, idx.aK) : 0;
+  if (!slab_map(idx, splits, 4, &g.slab)) return hipErrorInvalidValue;
   if (g.mp.pos[0] != 0) return hipErrorInvalidValue;  // A's lowest bit must belong to the chunk
   const int chunk = kAccChain / 16;
   const int64_t Mt = M / 128, Nt = N / 128;
-  const dim3 grid((unsigned)(Mt * Nt));
-  if (out && form == TN_GEMM_3M)
+  const dim3 grid((unsigned)(Mt * Nt * splits));
+  if (splits > 1) {
+    const int64_t kl = K / splits, n = M * N;
+    if (form == TN_GEMM_3M)
+      hipLaunchKernelGGL((k_cgemm128<TN_GEMM_3M, 1, NoOut>), grid, dim3(256), 0, s, A, B, work, N, K, kl, 0, kl, n, Mt,
+                         Nt, chunk, g, NoOut{});
+    else
+      hipLaunchKernelGGL((k_cgemm128<TN_GEMM_4M, 1, NoOut>), grid, dim3(256), 0, s, A, B, work, N, K, kl, 0, kl, n, Mt,
+                         Nt, chunk, g, NoOut{});
+    hipLaunchKernelGGL(k_splitk_sum, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 8192)), dim3(256), 0, s, work,
+                       C, n, splits);
+  } else if (out && form == TN_GEMM_3M)
     hipLaunchKernelGGL((k_cgemm128<TN_GEMM_3M, 1, OutMap>), grid, dim3(256), 0, s, A, B, C, N, K, K, 0, 0, 0, Mt, Nt,
                        chunk, g, *out);
   else if (out)

@@ -381,17 +381,20 @@ __global__ __launch_bounds__(512, 1) void k_hgemm_pp(const E* __restrict__ A, co
 // per thread and stage) held the kernel to 730 complex TFLOP/s on the rank-27 x
 // rank-25 pair, 1010 with eight 8-byte stores.  The stage's K offset
 // moves by a carrying add restricted to A's K bits above 4 (in increasing
-// positions).  B is [N][K] and C is [M][N], as in k_hgemm.
+// positions).  B is [N][K] and C is [M][N], as in k_hgemm; with W, slab z of
+// k_len terms goes there, unscaled in FP32.
 struct GatherAH {
   SkewMap mp;
   Runs aM;
   uint64_t maskK = 0, incK = 0;
+  SlabMap slab{};
 };
 
 template <int MODE, typename H, typename E, typename OM>
 __global__ __launch_bounds__(256, 2) void k_hgemm_ga(const E* __restrict__ A, const E* __restrict__ B,
-                                                   E* __restrict__ C, int64_t N, int64_t K, float out_scale,
-                                                   float* maxslot, int64_t Mt, int64_t Nt, const GatherAH g, const OM om) {
+                                                   E* __restrict__ C, float2* __restrict__ W, int64_t N, int64_t K,
+                                                   int64_t k_len, float out_scale, float* maxslot, int64_t Mt,
+                                                   int64_t Nt, const GatherAH g, const OM om) {
   typedef typename Frag<H>::T F;
   constexpr int BK = 32, BM = 128, BN = 128, LDK = BK + 8, P = 2, WTM = 2, WTN = 2;
   constexpr int NVB = BK / (256 / BN) / 4;  // B: uint4 loads per thread per stage
@@ -426,11 +429,11 @@ __global__ __launch_bounds__(256, 2) void k_hgemm_ga(const E* __restrict__ A, co
   const int row0 = (1 << (MODE == kQuadKR ? g.mp.mb[1] : MODE == kQuadKK ? 0 : g.mp.mb[0])) * LDK;
   const int row1 = MODE == kQuadRR ? (1 << g.mp.mb[1]) * LDK : 0;
   const uint64_t abase = dep_u<12>((uint64_t)bm, g.aM);
-  uint64_t kofs = 0;
+  uint64_t kofs = slab_offset(g.slab, z);
   const int brow = tid / 2, bk = (tid % 2) * 16;
   int64_t brow_b = bn + brow;
   if constexpr (has_out<OM>) brow_b = (int64_t)dep((uint64_t)brow_b, om.nmap);
-  const uint4* Bp = reinterpret_cast<const uint4*>(B + brow_b * K + bk);
+  const uint4* Bp = reinterpret_cast<const uint4*>(B + brow_b * K + z * k_len + bk);
   uint4 ra[4], rb[NVB];
   auto load_a = [&]() {
     const E* base = A + (abase + kofs);
@@ -483,7 +486,7 @@ __global__ __launch_bounds__(256, 2) void k_hgemm_ga(const E* __restrict__ A, co
   load_b(0);
   store_a(As[0]);
   store_stage<P, BN, LDK, NVB, H>(Bs[0], rb, brow, bk);
-  if (BK < K) {
+  if (BK < k_len) {
     kofs = ((kofs | ~g.maskK) + g.incK) & g.maskK;
     load_a();
     load_b(BK);
@@ -491,7 +494,7 @@ __global__ __launch_bounds__(256, 2) void k_hgemm_ga(const E* __restrict__ A, co
   __syncthreads();
   const int c = lane & 31, kq = (lane >> 5) * 8;
   int cur = 0;
-  for (int64_t k0 = 0; k0 < K; k0 += BK) {
+  for (int64_t k0 = 0; k0 < k_len; k0 += BK) {
 #pragma unroll
     for (int kk = 0; kk < BK; kk += 16) {
       F a[P][WTM], b[P][WTN];
@@ -524,10 +527,10 @@ __global__ __launch_bounds__(256, 2) void k_hgemm_ga(const E* __restrict__ A, co
         }
       }
     }
-    if (k0 + BK < K) {
+    if (k0 + BK < k_len) {
       store_a(As[cur ^ 1]);
       store_stage<P, BN, LDK, NVB, H>(Bs[cur ^ 1], rb, brow, bk);
-      if (k0 + 2 * BK < K) {
+      if (k0 + 2 * BK < k_len) {
         kofs = ((kofs | ~g.maskK) + g.incK) & g.maskK;
         load_a();
         load_b(k0 + 2 * BK);
@@ -570,58 +573,22 @@ __global__ __launch_bounds__(256, 2) void k_hgemm_ga(const E* __restrict__ A, co
         const int row = wm + 32 * i + 8 * (r >> 2) + 4 * kh + (r & 3);
         const int col = wn + 32 * j + c;
         const float re = acc[0][i][j][r], im = acc[1][i][j][r];
-        mx = mag_max(mx, re, im);
-        C[(bm + row) * N + bn + col] = from_f2<E>(re * out_scale, im * out_scale);
+        const int64_t o = (bm + row) * N + bn + col;
+        if (W) {
+          W[z * (Mt * BM * N) + o] = make_float2(re, im);
+        } else {
+          mx = mag_max(mx, re, im);
+          C[o] = from_f2<E>(re * out_scale, im * out_scale);
+        }
         if ((r & 15) == 15) __builtin_amdgcn_sched_barrier(0);
       }
-  record_max_in(maxslot, mx, reinterpret_cast<float*>(&As[0][0][0][0]));
+  if (!W) record_max_in(maxslot, mx, reinterpret_cast<float*>(&As[0][0][0][0]));
 }
 
 static uint64_t dep_host_h(uint64_t x, const Runs& r) {
   uint64_t o = 0;
   for (int i = 0; i < r.n; ++i) o |= ((x >> r.src[i]) & ((1ull << r.len[i]) - 1ull)) << r.dst[i];
   return o;
-}
-
-template <int MODE, typename H, typename E>
-static void hgemm_ga_launch(const E* A, const E* B, E* C, int64_t M, int64_t N, int64_t K, float scale,
-                            float* maxslot, const GatherAH& g, const OutMap* out, hipStream_t s) {
-  const int64_t Mt = M / 128, Nt = N / 128;
-  if (out)
-    hipLaunchKernelGGL((k_hgemm_ga<MODE, H, E, OutMap>), dim3((unsigned)(Mt * Nt)), dim3(256), 0, s, A, B, C, N, K,
-                       scale, maxslot, Mt, Nt, g, *out);
-  else
-    hipLaunchKernelGGL((k_hgemm_ga<MODE, H, E, NoOut>), dim3((unsigned)(Mt * Nt)), dim3(256), 0, s, A, B, C, N, K,
-                       scale, maxslot, Mt, Nt, g, NoOut{});
-}
-
-template <typename H, typename E>
-static hipError_t hgemm_ga_t(const E* A, const E* B, E* C, const IndexOp& idx, float scale, float* maxslot,
-                             const OutMap* out, hipStream_t s) {
-  const int64_t M = (int64_t)1 << idx.nM, N = (int64_t)1 << idx.nN, K = (int64_t)1 << idx.nK;
-  GatherAH g{};
-  if (!skew_map(idx, 5, 0, &g.mp) || g.mp.v != 12) return hipErrorInvalidValue;
-  g.aM = idx.aM;
-  g.maskK = dep_host_h((uint64_t)(K - 1) & ~(uint64_t)31, idx.aK);
-  g.incK = K > 32 ? dep_host_h(32, idx.aK) : 0;
-  switch (quad_mode(&g.mp, 2)) {
-    case kQuadKK: hgemm_ga_launch<kQuadKK, H, E>(A, B, C, M, N, K, scale, maxslot, g, out, s); break;
-    case kQuadKR: hgemm_ga_launch<kQuadKR, H, E>(A, B, C, M, N, K, scale, maxslot, g, out, s); break;
-    case kQuadRK: hgemm_ga_launch<kQuadRK, H, E>(A, B, C, M, N, K, scale, maxslot, g, out, s); break;
-    case kQuadRR: hgemm_ga_launch<kQuadRR, H, E>(A, B, C, M, N, K, scale, maxslot, g, out, s); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
-hipError_t launch_gemm_half_ga(int dtype, const void* A, const void* B, void* C, const IndexOp& idx, float out_scale,
-                               float* maxslot, hipStream_t s, const OutMap* out) {
-  if (!gemm_gather_ok(idx) || idx.nK < 5) return hipErrorInvalidValue;
-  if (dtype == TN_DTYPE_F16S)
-    return hgemm_ga_t<_Float16, cf16>((const cf16*)A, (const cf16*)B, (cf16*)C, idx, out_scale, maxslot, out, s);
-  if (dtype == TN_DTYPE_BF16S)
-    return hgemm_ga_t<__bf16, cbf16>((const cbf16*)A, (const cbf16*)B, (cbf16*)C, idx, out_scale, maxslot, out, s);
-  return hipErrorInvalidValue;
 }
 
 // C[i] = (sum over slabs s, in order, of W[s][i]) * scale, rounded to E.
@@ -640,6 +607,53 @@ __global__ __launch_bounds__(256) void k_hsplit_sum(const float2* __restrict__ W
     C[i] = from_f2<E>(r * out_scale, im * out_scale);
   }
   record_max(maxslot, mx);
+}
+
+template <int MODE, typename H, typename E>
+static void hgemm_ga_launch(const E* A, const E* B, E* C, float2* W, int64_t M, int64_t N, int64_t K, int splits,
+                            float scale, float* maxslot, const GatherAH& g, const OutMap* out, hipStream_t s) {
+  const int64_t Mt = M / 128, Nt = N / 128;
+  if (out)
+    hipLaunchKernelGGL((k_hgemm_ga<MODE, H, E, OutMap>), dim3((unsigned)(Mt * Nt)), dim3(256), 0, s, A, B, C, nullptr, N,
+                       K, K, scale, maxslot, Mt, Nt, g, *out);
+  else
+    hipLaunchKernelGGL((k_hgemm_ga<MODE, H, E, NoOut>), dim3((unsigned)(Mt * Nt * splits)), dim3(256), 0, s, A, B, C, W,
+                       N, K, K / splits, scale, maxslot, Mt, Nt, g, NoOut{});
+}
+
+template <typename H, typename E>
+static hipError_t hgemm_ga_t(const E* A, const E* B, E* C, const IndexOp& idx, float scale, float* maxslot,
+                             float2* W, int splits, const OutMap* out, hipStream_t s) {
+  const int64_t M = (int64_t)1 << idx.nM, N = (int64_t)1 << idx.nN, K = (int64_t)1 << idx.nK;
+  GatherAH g{};
+  if (!skew_map(idx, 5, 0, &g.mp) || g.mp.v != 12 || !slab_map(idx, splits, 5, &g.slab)) return hipErrorInvalidValue;
+  g.aM = idx.aM;
+  g.maskK = dep_host_h((uint64_t)(K - 1) & ~(uint64_t)31, idx.aK);
+  g.incK = K > 32 ? dep_host_h(32, idx.aK) : 0;
+  switch (quad_mode(&g.mp, 2)) {
+    case kQuadKK: hgemm_ga_launch<kQuadKK, H, E>(A, B, C, W, M, N, K, splits, scale, maxslot, g, out, s); break;
+    case kQuadKR: hgemm_ga_launch<kQuadKR, H, E>(A, B, C, W, M, N, K, splits, scale, maxslot, g, out, s); break;
+    case kQuadRK: hgemm_ga_launch<kQuadRK, H, E>(A, B, C, W, M, N, K, splits, scale, maxslot, g, out, s); break;
+    case kQuadRR: hgemm_ga_launch<kQuadRR, H, E>(A, B, C, W, M, N, K, splits, scale, maxslot, g, out, s); break;
+    default: return hipErrorInvalidValue;
+  }
+  if (splits > 1)
+    hipLaunchKernelGGL(k_hsplit_sum<E>, dim3((unsigned)std::min<int64_t>((M * N + 255) / 256, 8192)), dim3(256), 0, s, W,
+                       C, M * N, splits, scale, maxslot);
+  return hipGetLastError();
+}
+
+hipError_t launch_gemm_half_ga(int dtype, const void* A, const void* B, void* C, const IndexOp& idx, float out_scale,
+                               float* maxslot, hipStream_t s, float2* work, int splits, const OutMap* out) {
+  if (!gemm_gather_ok(idx) || idx.nK < 5 || (splits > 1 && (!work || out))) return hipErrorInvalidValue;
+  float2* W = splits > 1 ? work : nullptr;
+  if (dtype == TN_DTYPE_F16S)
+    return hgemm_ga_t<_Float16, cf16>((const cf16*)A, (const cf16*)B, (cf16*)C, idx, out_scale, maxslot, W, splits, out,
+                                      s);
+  if (dtype == TN_DTYPE_BF16S)
+    return hgemm_ga_t<__bf16, cbf16>((const cbf16*)A, (const cbf16*)B, (cbf16*)C, idx, out_scale, maxslot, W, splits,
+                                     out, s);
+  return hipErrorInvalidValue;
 }
 
 bool hgemm_shape_ok(int64_t M, int64_t N, int64_t K) {

@@ -294,9 +294,9 @@ inline int run_pos(const Runs& r, int j) {
 // 2^kGatherMinK terms read A in place instead of permuting it first, when
 // its layout admits that: 128 x 128 output tiles and chunks of 16 k (nM, nN
 // >= 7, nK >= 4), the chunk's 11 bits within A's low 32 positions, and the k
-// bits above 3 in increasing positions.  (The planner also requires at least
-// 512 output tiles when the sum has 2^11 terms or more, since the in-place
-// kernels do not split K.)
+// bits above 3 in increasing positions.  Long sums are split like any other
+// GEMM's: the slab's bits are the uppermost k bits, so a slab is an offset
+// into A.
 constexpr int kGatherMinLog2 = 20;
 constexpr int kGatherMinK = 5;
 inline bool gemm_gather_ok(const IndexOp& idx) {

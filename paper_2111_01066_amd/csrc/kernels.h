@@ -35,15 +35,17 @@ hipError_t launch_gemm_c64(const float2* A, const float2* B, float2* C, int64_t 
                            int64_t batch, int form, hipStream_t s, float2* work = nullptr, int splits = 1,
                            int tile = 0);
 // complex64 GEMM whose A is read in its stored layout through idx.aM / idx.aK
-// (B is [N][K], C is [M][N]; 128x128 tiles, no K split): the planner's
-// alternative to permuting A first (gemm_gather_ok must hold).
-// out: C in the order it describes (complex64: sums of at most kAccChain terms).
+// (B is [N][K], C is [M][N]; 128x128 tiles; splits a power of two, slabs in
+// `work`): the planner's alternative to permuting A first (gemm_gather_ok must
+// hold).
+// out: C in the order it describes (splits = 1; complex64: sums of at most kAccChain terms).
 hipError_t launch_gemm_c64_ga(const float2* A, const float2* B, float2* C, const IndexOp& idx, int form,
-                              hipStream_t s, const OutMap* out = nullptr);
+                              hipStream_t s, float2* work = nullptr, int splits = 1, const OutMap* out = nullptr);
 // the same for scaled FP16/BF16 (4M, 128x128 tiles, stages of 32 k; nK >= 5):
 // C = A B^T * out_scale, max |A B^T| recorded in *maxslot
 hipError_t launch_gemm_half_ga(int dtype, const void* A, const void* B, void* C, const IndexOp& idx, float out_scale,
-                               float* maxslot, hipStream_t s, const OutMap* out = nullptr);
+                               float* maxslot, hipStream_t s, float2* work = nullptr, int splits = 1,
+                               const OutMap* out = nullptr);
 // scaled FP16/BF16 GEMM on half MFMA; C = A B^T * out_scale; max |A B^T| recorded in *maxslot.
 // tile: 0 auto, 64 or 128; occ (128 tiles): 0 auto, 1 or 2 waves per SIMD, 3 the
 // ping-pong 256x128 kernel (4M, M % 256 == 0, K per split % 32 == 0).

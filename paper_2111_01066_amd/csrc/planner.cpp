@@ -771,10 +771,7 @@ int build_plan(PlanCore& P, std::string& err) {
       {
         std::vector<int> wa = MA;
         wa.insert(wa.end(), Kord.begin(), Kord.end());
-        // the in-place kernels have no K split: a long sum needs enough
-        // 128x128 output tiles (512, two per CU) on its own
-        const bool fills = nM + nN - 14 >= 9 || nK < 11;
-        if (wa != La && ra >= kGatherMinLog2 && nK >= kGatherMinK && fills &&
+        if (wa != La && ra >= kGatherMinLog2 && nK >= kGatherMinK &&
             (!half || P.opts.gemm_form != TN_GEMM_3M)) {
           gidx.nM = nM;
           gidx.nN = nN;
@@ -841,23 +838,30 @@ int build_plan(PlanCore& P, std::string& err) {
       }
       // split K when the output has too few tiles (128x128, or 64x64 when an
       // extent is 64) to fill the chip
-      if (nM >= 6 && nN >= 6 && !gather) {
+      if (nM >= 6 && nN >= 6) {
         const int tl = (nM >= 7 && nN >= 7) ? 7 : 6;
         const int64_t tiles = (int64_t)1 << (nM - tl + nN - tl);
         int sp = 1;
-        while (tiles * sp < 2048 && ((int64_t)1 << nK) / (sp * 2) >= 1024 && sp < 64 &&
+        // A in place: not split from two workgroups per CU (from one, below
+        // 2^11 terms) on its own.  Fewer used to permute A, or to leave CUs
+        // idle: complex64, 4096 x 256 over 2^12 290 us then, 240 split in
+        // place; 2048 x 128 over 2^10 (16 tiles) 265 unsplit, 83 in 4 slabs
+        const bool fills = gather && tiles >= (nK < 11 ? 256 : 512);
+        while (!fills && tiles * sp < 2048 && ((int64_t)1 << nK) / (sp * 2) >= 1024 && sp < 64 &&
                ((int64_t)sp * 2 << (nM + nN)) <= ((int64_t)1 << 28))
           sp *= 2;
         // and down to slabs of kSplitMinK terms while there are fewer than
         // two workgroups per CU (FP16, 256 x 128 outputs over 2^11 terms: 43
         // us in 2 slabs, 21 in 8; complex64, 4096 x 256 over 2^12: 276 us in
         // 4, 249 in 8)
-        while (tiles * sp < 512 && ((int64_t)1 << nK) / (sp * 2) >= kSplitMinK && sp < 64) sp *= 2;
+        while (!fills && tiles * sp < (gather && nK < 11 ? 256 : 512) &&
+               ((int64_t)1 << nK) / (sp * 2) >= kSplitMinK && sp < 64)
+          sp *= 2;
         // with tuning, room for every split the tuner may try: slabs of at
         // least 256 along K, at most 64 slabs, workspace <= 2^28 entries,
         // and only while the output has fewer than 8192 64x64 tiles
         int cap = sp;
-        if (P.opts.tune && ((int64_t)1 << (nM + nN - 12)) < 8192)
+        if (P.opts.tune && !gather && ((int64_t)1 << (nM + nN - 12)) < 8192)
           while (cap < 64 && ((int64_t)1 << nK) / (cap * 2) >= 256 &&
                  ((int64_t)cap * 2 << (nM + nN)) <= ((int64_t)1 << 28))
             cap *= 2;
@@ -1105,7 +1109,7 @@ void plan_fused_out(const PlanCore& P, FusedOut* F) {
   const Op& perm = P.ops[n_ops - 1];
   const Op& op = P.ops[n_ops - 2];
   const bool half = P.opts.dtype != TN_DTYPE_C64;
-  const bool gemm = op.kind == kOpGemm && op.gemm.gather_a;
+  const bool gemm = op.kind == kOpGemm && op.gemm.gather_a && op.gemm.split_k == 1;
   if (!gemm && op.kind != kOpSkew) return;
   // A skewed step reads A in shorter runs when its row tile also serves C's
   // order: worth it while A is at most four times C (2^22 rows, K = 32, 16
