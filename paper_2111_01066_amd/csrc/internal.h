@@ -289,7 +289,7 @@ inline int run_pos(const Runs& r, int j) {
     if (j >= r.src[i] && j < r.src[i] + r.len[i]) return r.dst[i] + (j - r.src[i]);
   return -1;
 }
-// GEMM steps whose large operand A (at least 2^kGatherMinLog2
+// GEMM steps whose large operand A (at least 2^gather_min_log2
 // entries) is not stored as [M bits, K bits] and whose sum has at least
 // 2^kGatherMinK terms read A in place instead of permuting it first, when
 // its layout admits that: 128 x 128 output tiles and chunks of 16 k (nM, nN
@@ -297,7 +297,13 @@ inline int run_pos(const Runs& r, int j) {
 // bits above 3 in increasing positions.  Long sums are split like any other
 // GEMM's: the slab's bits are the uppermost k bits, so a slab is an offset
 // into A.
-constexpr int kGatherMinLog2 = 20;
+// In FP16/BF16 that holds from 2^17 entries: permutes of that size cost a
+// launch each, and the 16-bit GEMM's 128 x 128 tiles are short (2^14 x 2^7 over
+// 2^5 30 us permuted, 20 in place; 2^10 x 2^7 over 2^8 41 and 28).  On the FP32
+// matrix cores too few large tiles cost more than the permute (within a
+// network, 2^12 x 2^8 over 2^6: 7 us more).  Tuned plans permute such an A:
+// their GEMM tiles and variants are timed, or come from the database.
+inline int gather_min_log2(bool half, bool tuned) { return half && !tuned ? 17 : 20; }
 constexpr int kGatherMinK = 5;
 inline bool gemm_gather_ok(const IndexOp& idx) {
   if (idx.nM < 7 || idx.nN < 7 || idx.nK < 4) return false;

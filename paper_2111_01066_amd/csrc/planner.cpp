@@ -771,7 +771,7 @@ int build_plan(PlanCore& P, std::string& err) {
       {
         std::vector<int> wa = MA;
         wa.insert(wa.end(), Kord.begin(), Kord.end());
-        if (wa != La && ra >= kGatherMinLog2 && nK >= kGatherMinK &&
+        if (wa != La && ra >= gather_min_log2(half, P.opts.tune) && nK >= kGatherMinK &&
             (!half || P.opts.gemm_form != TN_GEMM_3M)) {
           gidx.nM = nM;
           gidx.nN = nN;

@@ -1,6 +1,7 @@
-"""GEMMs that read A in place with their sum split in slabs: one to many slabs
-of one and more output tiles, random orders of all three tensors, against FP64
-sums of the same rounded inputs (bounds as in test_gpu_half_layouts)."""
+"""GEMMs that read A in place with their sum split in slabs (one to many slabs
+of one and more output tiles) or with the smallest A that is read in place:
+random orders of all three tensors, against FP64 sums of the same rounded
+inputs (bounds as in test_gpu_half_layouts)."""
 import numpy as np
 import pytest
 
@@ -11,6 +12,9 @@ from tests.test_gpu_half_layouts import UNIT, _offsets, _product  # noqa: E402
 
 # rows, columns, terms (log2) and the slabs that the planner takes
 SHAPES = [((11, 7, 9), 2), ((10, 7, 10), 4), ((9, 8, 11), 8), ((7, 7, 13), 32), ((8, 9, 12), 16), ((11, 11, 11), 2)]
+
+# the smallest 16-bit A read in place (2^17 entries), few tiles of short sums
+SMALL = [(10, 7, 7), (9, 8, 8), (12, 7, 5)]
 
 
 def _labels(shape, seed):
@@ -30,10 +34,21 @@ def test_planned_slabs(dtype, form, shape, slabs):
         assert [(o["ga"], o["split_k"], o["split_max"]) for o in g] == [(1, slabs, slabs)]
 
 
+@pytest.mark.parametrize("dtype", ["c64", "f16s", "bf16s"])
+def test_smallest_a_read_in_place(dtype):
+    def ga(shape):
+        _, (la, lb, lc) = _labels(shape, 0)
+        pp = tnrcs.PairPlan(la, lb, lc, dtype=dtype, dry_run=True)
+        return [o["ga"] for o in pp.json()["ops"] if o["kind"] == 1]
+
+    assert all(ga(s) == [int(dtype != "c64")] for s in SMALL)
+    assert ga((9, 7, 7)) == [0] and ga((13, 7, 7)) == [1]
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype,form", [("c64", "3m"), ("c64", "4m"), ("f16s", "4m"), ("bf16s", "4m")])
 @pytest.mark.parametrize("seed", [0, 1])
-@pytest.mark.parametrize("shape", [s for s, _ in SHAPES])
+@pytest.mark.parametrize("shape", [s for s, _ in SHAPES] + SMALL)
 def test_slabs_of_a_read_in_place(dtype, form, seed, shape):
     nM, nN, nK = shape
     rng, (la, lb, lc) = _labels(shape, seed)
