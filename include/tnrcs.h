@@ -84,7 +84,8 @@ typedef struct {
   int32_t dtype;          /* TN_DTYPE_* */
   int32_t gemm_form;      /* TN_GEMM_* */
   int32_t max_log2;       /* reject plans with a per-slice tensor above 2^max_log2 elements (0: no bound) */
-  int32_t use_graph;      /* 1: run each slice as one replay of a captured HIP graph */
+  int32_t use_graph;      /* 1: run each slice as one replay of a captured HIP graph (small networks,
+                             JSON "small_net", run all slices in one launch instead) */
   int32_t dry_run;        /* 1: plan on the host only; no device calls, no device memory */
   int32_t device;         /* HIP device ordinal */
   int32_t host_fold_log2; /* steps whose result has at most 2^host_fold_log2 entries and whose operands
@@ -232,7 +233,8 @@ typedef struct tn_batch_s* tn_batch_t;
  * run one after the other, in the order given, in one lane; plans on
  * separate arenas may go to separate lanes (at most 4).  In a lane, each
  * plan sets its slice cursor and replays its per-slice HIP graph (captured
- * here for every plan with opts.use_graph) once per slice.  Each lane runs
+ * here for every plan with opts.use_graph that is not a small network) once
+ * per slice.  Each lane runs
  * on a stream of the batch (default priority) that starts after the
  * caller's stream's earlier work and that the caller's stream waits for, so
  * lanes run side by side.  The plans and amplitude buffers must
