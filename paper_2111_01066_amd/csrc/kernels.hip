@@ -904,10 +904,14 @@ __global__ __launch_bounds__(256) void k_splitk_part(const E* __restrict__ A, co
 
 // Sums the block partials of group blockIdx.x.  Thread (slice, output): the
 // outputs are consecutive threads, so a slice reads whole runs of partials;
-// 1024 / nout slices take the blocks in turn, then add up in a fixed tree.
-// (Summed output after output by 256 threads, 64 outputs of 512 blocks took
-// 70 us; 6 us now.)
+// 1024 / nout slices take the blocks in turn, each in kFinalChains sums, then
+// all add up in a fixed tree.  (Summed output after output by 256 threads, 64
+// outputs of 512 blocks took 70 us; 6 us now.)
+// The separate sums keep a serial chain to 4 partials at most (1024 blocks, 64
+// outputs), as with a thread per 256th block; one chain per thread would
+// be 64 long there, and its rounding error twice as large.
 constexpr int kFinalThreads = 1024;
+constexpr int kFinalChains = 16;
 
 template <typename E>
 __global__ __launch_bounds__(kFinalThreads) void k_splitk_final(const float2* __restrict__ part, int nblk, int ln_out,
@@ -924,14 +928,24 @@ __global__ __launch_bounds__(kFinalThreads) void k_splitk_final(const float2* __
     const int64_t im = grp >> gn_bits, in = grp & ((1 << gn_bits) - 1);
     C += ((im << lm_sub) << ln_row) | (in << ln_sub);
   }
-  float r = 0.f, i = 0.f;
-#pragma unroll 8
-  for (int g = slice; g < nblk; g += slices) {
-    const float2 v = part[((int64_t)g << ln_out) | o];
-    r += v.x;
-    i += v.y;
+  float r[kFinalChains] = {}, i[kFinalChains] = {};
+  for (int g = slice; g < nblk; g += slices * kFinalChains) {
+#pragma unroll
+    for (int q = 0; q < kFinalChains; ++q) {
+      if (g + q * slices >= nblk) break;
+      const float2 v = part[((int64_t)(g + q * slices) << ln_out) | o];
+      r[q] += v.x;
+      i[q] += v.y;
+    }
   }
-  red[tid] = make_float2(r, i);
+#pragma unroll
+  for (int w = kFinalChains >> 1; w > 0; w >>= 1)
+#pragma unroll
+    for (int q = 0; q < w; ++q) {
+      r[q] += r[q + w];
+      i[q] += i[q + w];
+    }
+  red[tid] = make_float2(r[0], i[0]);
   __syncthreads();
   for (int w = slices >> 1; w > 0; w >>= 1) {
     if (slice < w) {
