@@ -100,6 +100,29 @@ __device__ __forceinline__ float small_blocks(const SmallOp& op, E* T, const uin
   return mx;
 }
 
+// A lane's sum of up to 2^10 terms, four at a time, in a tree of degree four
+// (a chain of 2^9 terms would round 2^10 times in a row; this as often as a
+// split sum of a few terms per thread and a tree over the threads).
+struct SumTree {
+  float2 s[5] = {};
+  // adds the g-th (from 1) group of four
+  __device__ __forceinline__ void add(float re, float im, int g) {
+    s[0].x += re;
+    s[0].y += im;
+#pragma unroll
+    for (int l = 1; l < 5; ++l) {
+      if (g & ((1 << 2 * l) - 1)) break;
+      s[l].x += s[l - 1].x;
+      s[l].y += s[l - 1].y;
+      s[l - 1] = make_float2(0.f, 0.f);
+    }
+  }
+  __device__ __forceinline__ void total(float& re, float& im) const {
+    re = ((s[0].x + s[1].x) + (s[2].x + s[3].x)) + s[4].x;
+    im = ((s[0].y + s[1].y) + (s[2].y + s[3].y)) + s[4].y;
+  }
+};
+
 struct SmallShape {
   int32_t n_ops, n_leaves, n_tabs, elems, root, root_tab, n_open, n_slots, pad_elems;
 };
@@ -172,13 +195,24 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(const E* __restrict__ l
           const E* A = T + op.a + tm[c >> op.nN];
           const E* B = T + op.b + tn[c & ((1 << op.nN) - 1)];
           float re = 0.f, im = 0.f;
-#pragma unroll 4
-          for (int k = t; k < K; k += 1 << L) {
+          auto madd = [&](int k, float& r, float& s) {
             const float2 x = to_f2(A[ka[k]]), y = to_f2(B[kb[k]]);
-            re = fmaf(x.x, y.x, re);
-            re = fmaf(-x.y, y.y, re);
-            im = fmaf(x.x, y.y, im);
-            im = fmaf(x.y, y.x, im);
+            r = fmaf(x.x, y.x, r);
+            r = fmaf(-x.y, y.y, r);
+            s = fmaf(x.x, y.y, s);
+            s = fmaf(x.y, y.x, s);
+          };
+          if (K >> L < 4) {
+            for (int k = t; k < K; k += 1 << L) madd(k, re, im);
+          } else {
+            SumTree sum;
+            for (int k = t, g = 1; k < K; k += 4 << L, ++g) {
+              float r = 0.f, s = 0.f;
+#pragma unroll
+              for (int q = 0; q < 4; ++q) madd(k + (q << L), r, s);
+              sum.add(r, s, g);
+            }
+            sum.total(re, im);
           }
           for (int q = 1 << L >> 1; q > 0; q >>= 1) {
             re += __shfl_xor(re, q);
