@@ -99,7 +99,10 @@ typedef struct {
                              caller-owned device workspace of arena_bytes bytes (256-byte aligned)
                              used for every intermediate; several plans may share one workspace as
                              long as their runs are ordered (one stream, or a batch below).  It must
-                             outlive the plan.  tn_plan fails with TN_E_MEM if it is too small. */
+                             outlive the plan.  tn_plan fails with TN_E_MEM if it is too small.
+                             (A plan that would not fit the budget or workspace leaves out the
+                             scratch that only gains speed; a dry run with arena_bytes > 0 does so
+                             too, and reports what it then needs.) */
   const char* tune_db;    /* with tune: a text file caching tuning results across processes (read
                              at the first use of a path, new results appended); NULL: the results
                              are kept for the life of the process only */

@@ -606,6 +606,22 @@ static int tune_classes(PlanCore& P, bool measure) {
   return rc ? fail(rc, "rebuild after class tuning: " + err) : TN_OK;
 }
 
+// Bytes that the plan takes of a budget: a caller's workspace holds the arena
+// alone.
+static int64_t budget_bytes(const PlanCore& P) {
+  return ((P.opts.arena ? 0 : P.leaves_elems + P.bound_elems) + P.arena_elems) * (int64_t)elem_bytes_of(P.opts.dtype);
+}
+
+// Plans again without the scratch that only gains speed when the plan would
+// not fit the budget.
+static int fit_budget(PlanCore& P, int64_t budget) {
+  if (budget_bytes(P) <= budget) return TN_OK;
+  P.lean = true;
+  std::string err;
+  int rc = build_plan(P, err);
+  return rc ? fail(rc, err) : TN_OK;
+}
+
 static void drop_graph(tn_plan_s* p) {
   if (p->exec) hipGraphExecDestroy(p->exec);
   if (p->graph) hipGraphDestroy(p->graph);
@@ -706,6 +722,10 @@ int tn_plan(const tn_circuit* c, const int32_t* order_pairs, int32_t n_steps, co
       delete p;
       return rc;
     }
+    if (o.arena_bytes > 0 && (rc = fit_budget(P, o.arena_bytes))) {
+      delete p;
+      return rc;
+    }
     if (o.dtype != TN_DTYPE_C64) leaf_exponents(P);
     propagate_exponents(P);
     *out = p;
@@ -724,15 +744,15 @@ int tn_plan(const tn_circuit* c, const int32_t* order_pairs, int32_t n_steps, co
   e = hipMemGetInfo(&free_b, &total_b);
   if (e != hipSuccess) return bail(hip_fail(e, "hipMemGetInfo"));
   const bool ext_arena = o.arena != nullptr;
-  if (ext_arena) {
-    if ((reinterpret_cast<uintptr_t>(o.arena) & 255) != 0) return bail(fail(TN_E_ARG, "arena not 256-byte aligned"));
-    if (P.arena_elems * (int64_t)p->eb > o.arena_bytes)
-      return bail(fail(TN_E_MEM, "plan needs an arena of " + std::to_string(P.arena_elems * (int64_t)p->eb) +
-                                     " bytes, workspace has " + std::to_string(o.arena_bytes)));
-  }
+  if (ext_arena && (reinterpret_cast<uintptr_t>(o.arena) & 255) != 0)
+    return bail(fail(TN_E_ARG, "arena not 256-byte aligned"));
+  const int64_t mem = (int64_t)(0.92 * (double)free_b);
+  if ((rc = fit_budget(P, ext_arena || o.arena_bytes > 0 ? o.arena_bytes : mem))) return bail(rc);
+  if (ext_arena && P.arena_elems * (int64_t)p->eb > o.arena_bytes)
+    return bail(fail(TN_E_MEM, "plan needs an arena of " + std::to_string(P.arena_elems * (int64_t)p->eb) +
+                                   " bytes, workspace has " + std::to_string(o.arena_bytes)));
   const int64_t need = ((ext_arena ? 0 : P.arena_elems) + P.leaves_elems + P.bound_elems) * (int64_t)p->eb;
-  const int64_t budget =
-      (!ext_arena && o.arena_bytes > 0) ? o.arena_bytes : (int64_t)(0.92 * (double)free_b);
+  const int64_t budget = (!ext_arena && o.arena_bytes > 0) ? o.arena_bytes : mem;
   if (need > budget)
     return bail(fail(TN_E_MEM, "plan needs " + std::to_string(need) + " device bytes, budget " + std::to_string(budget)));
   auto dmalloc = [&](void** ptr, int64_t bytes, const char* what) -> int {

@@ -218,6 +218,10 @@ struct PlanCore {
   SmallNet small;
   std::string json;
 
+  // leave out the scratch that only gains speed (slabs of short GEMM sums, a
+  // copy of a small operand): plans whose workspace or budget would not hold it
+  bool lean = false;
+
   // kernel class per device step: the planner's rule unless the autotuner
   // measured another valid class to be faster (step -> OpKind)
   std::map<int, int> class_override;

@@ -854,7 +854,7 @@ int build_plan(PlanCore& P, std::string& err) {
         // two workgroups per CU (FP16, 256 x 128 outputs over 2^11 terms: 43
         // us in 2 slabs, 21 in 8; complex64, 4096 x 256 over 2^12: 276 us in
         // 4, 249 in 8)
-        while (!fills && tiles * sp < (gather && nK < 11 ? 256 : 512) &&
+        while (!fills && !P.lean && tiles * sp < (gather && nK < 11 ? 256 : 512) &&
                ((int64_t)1 << nK) / (sp * 2) >= kSplitMinK && sp < 64)
           sp *= 2;
         // with tuning, room for every split the tuner may try: slabs of at
@@ -907,7 +907,15 @@ int build_plan(PlanCore& P, std::string& err) {
       // (of 2^12 entries or more) is first permuted to [free wires, K]
       int tmp[2] = {-1, -1};
       std::vector<int> lay2[2] = {La, Lb};
-      if (half && cls == kOpSkew && nK >= 4) K = quad_order(La, K, 4);
+      if (half && cls == kOpSkew && nK >= 4) {
+        const std::vector<int> Kq = quad_order(La, K, 4);
+        auto b_aligned = [&](const std::vector<int>& Ko) {
+          bool ok = true;
+          for (int i = 0; i < std::min(nK, 8); ++i) ok &= pos_in(Lb, Ko[nK - 1 - i]) == i;
+          return ok;
+        };
+        if (!(P.lean && nK >= 7 && b_aligned(K) && !b_aligned(Kq))) K = Kq;
+      }
       // the matrix-core skewed kernel with a long sum stages B chunk by
       // chunk: a B whose low k bits are scattered is permuted first too
       // (B only; A is read in place)
