@@ -478,7 +478,9 @@ static int time_class(const PlanCore& P, const std::vector<int>& a, const std::v
   Q.pair_b = b;
   Q.pair_out = c;
   Q.opts = P.opts;
-  Q.opts.tune = 0;
+  Q.opts.tune = 0;  // no recursion; the step's forms are the tuned plan's all the same
+  Q.tuned_forms = true;
+  Q.lean = P.lean;
   Q.opts.arena = nullptr;
   Q.opts.arena_bytes = 0;
   Q.class_override[0] = cls;

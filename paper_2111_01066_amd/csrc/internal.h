@@ -218,6 +218,10 @@ struct PlanCore {
   SmallNet small;
   std::string json;
 
+  // plan the forms of a tuned plan (gather_min_log2): set with opts.tune, and
+  // for the one-step plans that the class tuner times for it
+  bool tuned_forms = false;
+
   // leave out the scratch that only gains speed (slabs of short GEMM sums, a
   // copy of a small operand): plans whose workspace or budget would not hold it
   bool lean = false;

@@ -503,6 +503,7 @@ static void build_small(PlanCore& P, const std::vector<SmallStep>& steps, const 
 
 int build_plan(PlanCore& P, std::string& err) {
   const int n = P.n_qubits;
+  if (P.opts.tune) P.tuned_forms = true;
   std::vector<HostTensor> leaves;
   int rc = P.pair_mode ? build_pair_network(P, leaves, err) : build_network(P, leaves, err);
   if (rc) return rc;
@@ -771,7 +772,7 @@ int build_plan(PlanCore& P, std::string& err) {
       {
         std::vector<int> wa = MA;
         wa.insert(wa.end(), Kord.begin(), Kord.end());
-        if (wa != La && ra >= gather_min_log2(half, P.opts.tune) && nK >= kGatherMinK &&
+        if (wa != La && ra >= gather_min_log2(half, P.tuned_forms) && nK >= kGatherMinK &&
             (!half || P.opts.gemm_form != TN_GEMM_3M)) {
           gidx.nM = nM;
           gidx.nN = nN;
