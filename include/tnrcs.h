@@ -296,7 +296,9 @@ int tn_plan_set_output_bits(tn_plan_t p, const uint8_t* out_bits);
  * kernel; synchronizes and writes each kernel's duration in milliseconds to
  * op_ms[0..n) in plan order (the per-step kernels, then the accumulation).
  * *n_ops receives the kernel count; cap is op_ms's capacity.  Measurement
- * support for benchmarks; the slice result is the same as in the graph path. */
+ * support for benchmarks; the slice result is the same as in the graph path.
+ * For a small network (JSON "small_net") these are the times of the listed
+ * kernels run one by one, which tn_contract_slices replaces by one launch. */
 int tn_plan_profile(tn_plan_t p, int64_t slice, void* amp, void* stream, float* op_ms, int32_t cap,
                     int32_t* n_ops);
 
