@@ -114,7 +114,7 @@ typedef struct {
   int32_t n_leaves;        /* canonical leaves */
   int32_t n_host_steps;    /* steps folded on the host at plan time */
   int32_t n_device_steps;  /* steps run per slice */
-  int32_t n_kernels;       /* kernel launches per slice */
+  int32_t n_kernels;       /* kernel launches per slice (small networks, JSON "small_net": 1) */
   int32_t max_log2;        /* largest per-slice device tensor, log2 elements */
   int32_t n_open;
   double flops_per_slice;  /* sum over device steps of 8*M*N*K */
@@ -122,7 +122,8 @@ typedef struct {
   double moved_per_slice;  /* bytes the chosen kernels move, extra permute traffic included */
   int64_t arena_bytes;     /* device arena for intermediates and permute scratch */
   int64_t leaf_bytes;      /* device leaves (all slices) */
-  int32_t n_dense, n_skinny, n_generic, n_permute; /* kernel-class counts per slice */
+  int32_t n_dense, n_skinny, n_generic, n_permute; /* kernel-class counts per slice (these and
+                              moved_per_slice: of the listed kernels, also in small networks) */
   int32_t k_hist[64];      /* histogram of contracted-index count |K| over device steps */
 } tn_plan_stats;
 

@@ -836,7 +836,7 @@ int tn_pair_plan(int32_t rank_a, const int32_t* labels_a, int32_t rank_b, const 
   };
   hipError_t e = hipSetDevice(o.device);
   if (e != hipSuccess) return bail(hip_fail(e, "hipSetDevice"));
-  if ((e = hipMalloc((void**)&p->d_arena, (size_t)std::max<int64_t>(P.arena_elems * p->eb, 256))) != hipSuccess ||
+  if ((e = hipMalloc((void**)&p->d_arena, (size_t)std::max<int64_t>(P.arena_alloc * p->eb, 256))) != hipSuccess ||
       (e = hipMalloc((void**)&p->d_maxslots, (size_t)std::max(P.n_slots, 1) * 4)) != hipSuccess)
     return bail(hip_fail(e, "alloc pair workspace"));
   std::vector<float> zero(std::max(P.n_slots, 1), 0.f);

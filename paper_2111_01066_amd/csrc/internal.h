@@ -211,6 +211,7 @@ struct PlanCore {
   std::vector<Op> ops;
   AccumDesc accum;
   int64_t arena_elems = 0;
+  int64_t arena_alloc = 0;  // what launches touch: less than arena_elems where a listed op is fused away
   int32_t root_is_leaf = 0;
   std::vector<int> root_layout;  // layout of the final tensor (wires, most significant first)
   int32_t n_slots = 0;  // producing ops with a magnitude record (scaled storage)

@@ -997,7 +997,7 @@ int build_plan(PlanCore& P, std::string& err) {
     dstep++;
   }
   // arena placement
-  P.arena_elems = place_buffers(bufs);
+  P.arena_elems = P.arena_alloc = place_buffers(bufs);
   for (auto& f : fix) {
     Op& op = P.ops[f.op];
     TRef r{kArena, bufs[f.buf].off};
@@ -1041,7 +1041,7 @@ int build_plan(PlanCore& P, std::string& err) {
   st.n_leaves = L;
   st.n_host_steps = P.n_host_steps;
   st.n_device_steps = dstep;
-  st.n_kernels = (int)P.ops.size() + 1 + (P.binds.empty() ? 0 : 1);
+  st.n_kernels = P.small.ok ? 1 : (int)P.ops.size() + 1 + (P.binds.empty() ? 0 : 1);
   st.max_log2 = max_log2;
   st.n_open = (int)P.open_wires.size();
   st.arena_bytes = P.arena_elems * elem_bytes_plan(P);
@@ -1107,6 +1107,24 @@ int build_pair_plan(PlanCore& P, std::string& err) {
   }
   P.stats.n_kernels = (int)P.ops.size();
   plan_fused_out(P, &P.fused);
+  if (P.fused.ok) {
+    // the listed permute and the tensor that it reads are left out: that
+    // tensor moves to the end of the arena, past what is allocated
+    const Op& perm = P.ops.back();
+    P.stats.n_kernels--;
+    P.stats.n_permute--;
+    P.stats.moved_per_slice -= perm.bytes;
+    const int64_t off = perm.a.off, n = align_up((int64_t)1 << perm.perm.rank, 64);
+    P.arena_alloc = P.arena_elems - n;
+    P.stats.arena_bytes = P.arena_alloc * elem_bytes_plan(P);
+    auto move = [&](TRef& r) {  // (one step: no two buffers of the arena overlap)
+      if (r.region != kArena || r.off < off) return;
+      r.off = r.off == off ? P.arena_alloc : r.off - n;
+    };
+    for (Op& op : P.ops)
+      for (TRef* r : {&op.a, &op.b, &op.c, &op.w}) move(*r);
+    move(P.accum.root);
+  }
   make_json(P);
   return TN_OK;
 }
