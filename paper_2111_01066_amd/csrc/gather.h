@@ -90,8 +90,8 @@ __device__ __forceinline__ void skew_split(const SkewMap& mp, int e, uint64_t& o
 // them together: the k bits that the load does not cover are the ones that
 // tell the thread's loads apart.  How they sit: kQuadKK: the load covers k0,
 // k1; kQuadKR: k0, then a row bit; kQuadRK: a row bit, then k0; kQuadRR: two
-// row bits.
-enum QuadMode : int { kQuadKK = 0, kQuadKR = 1, kQuadRK = 2, kQuadRR = 3 };
+// row bits.  kQuadNone: entries stored one by one.
+enum QuadMode : int { kQuadNone = -1, kQuadKK = 0, kQuadKR = 1, kQuadRK = 2, kQuadRR = 3 };
 
 // Host: the mode of a chunk map (entries sorted by position), whose entries
 // are reordered so that the last ones tell a thread's 2^lj loads apart: k1

@@ -69,6 +69,7 @@ struct IndexOp {
   // skinny tiling (planner-chosen): the tile holds the low tM M-bits and the
   // low tK K-bits of the chunk; the remaining bits index tiles / chunks.
   int32_t tM = 0, tK = 0;
+  int32_t quad = 0;       // FP16/BF16 skewed steps: K ordered for four-k stores (gather.h, QuadMode)
   float out_scale = 1.f;  // scaled storage: 2^-s applied before rounding
 };
 

@@ -148,6 +148,49 @@ std::vector<int> quad_order(const std::vector<int>& La, const std::vector<int>& 
   return out;
 }
 
+// Whether the lowest 8 bits of K (or all, if fewer) are the tensor's lowest, in order.
+bool k_aligned(const std::vector<int>& have, const std::vector<int>& K) {
+  const int nK = (int)K.size();
+  for (int i = 0; i < std::min(nK, 8); ++i)
+    if (pos_in(have, K[nK - 1 - i]) != i) return false;
+  return true;
+}
+
+// Whether a 16-bit skewed step of nK >= 4 takes its K in quad_order (Kq) and
+// stores four k together, or keeps A's order (K) and stores entry by entry.
+// * nK >= 7: four k together (FP16, 2^21 to 2^24 rows over 2^7 terms: 0.6 to
+//   0.97 of the time), unless that order alone makes a permute of B
+//   necessary (of 2^12 entries or more) and A is below 2^27 entries: the
+//   permute's 4 to 5 us are more than is gained (2^10 rows x 2^5 over 2^8:
+//   15.7 us entry by entry, 19.5 us; 2^19 x 2^5 over 2^8: 127 and 118).
+// * nK = 6: four k together (0.6 to 1.0 of the time).
+// * nK = 4, 5: four k together where the stores bound the step.  A narrow
+//   store hits each LDS bank eight times when the lowest 8 bits of A (2 within a
+//   load, 6 across the lanes of a wave) are rows: 2^22 x 2^5 over 2^4 193 us,
+//   165 with the wide ones; 2^23 x 2^4 over 2^5 560, 355.  With one k bit there
+//   it does so up to 16 columns (2^20 x 2^4 over 2^5 0.91 of the time), less in large
+//   tensors when that bit is a lane's (2^26 x 2^4 over 2^4 1.92 ms, 2.04).  With more
+//   the wide stores win where A is small enough for the caches (0.92 to
+//   0.99 of the time below 2^24 entries over 2^4 terms, below 2^18 over 2^5) and over 2^4 terms into
+//   up to 8 columns (2^21 x 2^3 123 us, 107); in larger steps the narrow ones are
+//   hidden behind the loads, and the wide ones, though fewer, made the whole step slower (2^25 x
+//   2^4 over 2^4 0.91 ms, 1.06; 2^26 x 2^4 over 2^5 2.53, 2.93).
+bool skew_quad(const std::vector<int>& La, const std::vector<int>& Lb, const std::vector<int>& K,
+               const std::vector<int>& Kq, int nN, bool lean) {
+  const int nK = (int)K.size();
+  if (nK >= 7) {
+    const bool permutes = Lb.size() >= 12 && k_aligned(Lb, K) && !k_aligned(Lb, Kq);
+    return !(permutes && (lean || La.size() < 27));
+  }
+  if (nK == 6) return true;
+  auto below = [&](int bits) {
+    return std::count_if(K.begin(), K.end(), [&](int w) { return pos_in(La, w) < bits; });
+  };
+  const int ra = (int)La.size();
+  if (below(8) == 0 || ra < (nK == 4 ? 24 : 18) || (nK == 4 && nN <= 3)) return true;
+  return below(8) == 1 && nN <= 4 && (below(2) == 1 || ra < 28);
+}
+
 struct Buf {
   int64_t elems;
   int t0, t1;
@@ -323,7 +366,7 @@ void make_json(PlanCore& P) {
       json_runs(js, op.idx.bN);
       js << ",\"bK\":";
       json_runs(js, op.idx.bK);
-      js << ",\"tM\":" << op.idx.tM << ",\"tK\":" << op.idx.tK << ",\"s_out\":" << op.s_out << ",\"w\":";
+      js << ",\"tM\":" << op.idx.tM << ",\"tK\":" << op.idx.tK << ",\"quad\":" << op.idx.quad << ",\"s_out\":" << op.s_out << ",\"w\":";
       json_ref(js, op.w);
     }
     js << "}";
@@ -910,12 +953,8 @@ int build_plan(PlanCore& P, std::string& err) {
       std::vector<int> lay2[2] = {La, Lb};
       if (half && cls == kOpSkew && nK >= 4) {
         const std::vector<int> Kq = quad_order(La, K, 4);
-        auto b_aligned = [&](const std::vector<int>& Ko) {
-          bool ok = true;
-          for (int i = 0; i < std::min(nK, 8); ++i) ok &= pos_in(Lb, Ko[nK - 1 - i]) == i;
-          return ok;
-        };
-        if (!(P.lean && nK >= 7 && b_aligned(K) && !b_aligned(Kq))) K = Kq;
+        g.idx.quad = skew_quad(La, Lb, K, Kq, nN, P.lean);
+        if (g.idx.quad) K = Kq;
       }
       // the matrix-core skewed kernel with a long sum stages B chunk by
       // chunk: a B whose low k bits are scattered is permuted first too
@@ -925,9 +964,7 @@ int build_plan(PlanCore& P, std::string& err) {
         for (int side = skew_long ? 1 : 0; side < 2; ++side) {
           const std::vector<int>& have = side ? Lb : La;
           const int r = (int)have.size();
-          bool aligned = true;
-          for (int i = 0; i < std::min(nK, 8); ++i) aligned &= pos_in(have, K[nK - 1 - i]) == i;
-          if (aligned || r < 12) continue;
+          if (r < 12 || k_aligned(have, K)) continue;
           std::vector<int> want = side ? NB : MA;
           want.insert(want.end(), K.begin(), K.end());
           Op op;

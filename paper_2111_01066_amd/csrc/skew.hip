@@ -510,16 +510,20 @@ struct SkewHalf<cbf16> {
 // they hold four k of two rows; those of kQuadRR differ in k0: two k of four
 // rows.  (Sixteen 2-byte stores per thread and chunk instead of four to eight
 // wider ones held the K = 512 step of 2^20 rows to 2.0 TB/s; 3.4 now.)
+// kQuadNone stores them one by one: the planner's choice (op.quad) where the
+// wide stores measured slower.
 template <int VEC, int MODE, int LPT, typename E, typename H>
 __device__ __forceinline__ void skew_store_half(H* s, const E (&v)[LPT][VEC], const int (&eidx)[LPT][VEC], int row0,
                                                 int row1) {
   constexpr int IM = kSkewPM * kSkewHS;
-  if constexpr (VEC == 1) {
+  if constexpr (MODE == kQuadNone) {
 #pragma unroll
-    for (int j = 0; j < LPT; ++j) {
-      s[eidx[j][0]] = v[j][0].re;
-      s[IM + eidx[j][0]] = v[j][0].im;
-    }
+    for (int j = 0; j < LPT; ++j)
+#pragma unroll
+      for (int u = 0; u < VEC; ++u) {
+        s[eidx[j][u]] = v[j][u].re;
+        s[IM + eidx[j][u]] = v[j][u].im;
+      }
   } else {
     static_assert(LPT == 2 && VEC == 4, "two loads of four entries");
     uint32_t w[2][4];
@@ -571,7 +575,7 @@ __global__ __launch_bounds__(256, 2) void k_skew_ph(const E* __restrict__ A, con
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = lane & 31, kh = lane >> 5;
   // LDS offsets of the row bits that a 16-byte load covers
-  const int row0 = (1 << (MODE == kQuadKR ? mp.mb[1] : MODE == kQuadKK ? 0 : mp.mb[0])) * kSkewHS;
+  const int row0 = (1 << (MODE == kQuadKR ? mp.mb[1] : MODE <= kQuadKK ? 0 : mp.mb[0])) * kSkewHS;
   const int row1 = MODE == kQuadRR ? (1 << mp.mb[1]) * kSkewHS : 0;
   if (tid < 64) bn[tid] = tid < N ? dep((uint64_t)tid, op.bN) : 0;
   // C in the caller's order: staging area, this lane's entries in it, offsets
@@ -738,7 +742,7 @@ __global__ __launch_bounds__(256, 2) void k_skew_phc(const E* __restrict__ A, co
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = lane & 31, kh = lane >> 5;
   // LDS offsets of the row bits that a 16-byte load covers
-  const int row0 = (1 << (MODE == kQuadKR ? mp.mb[1] : MODE == kQuadKK ? 0 : mp.mb[0])) * kSkewHS;
+  const int row0 = (1 << (MODE == kQuadKR ? mp.mb[1] : MODE <= kQuadKK ? 0 : mp.mb[0])) * kSkewHS;
   const int row1 = MODE == kQuadRR ? (1 << mp.mb[1]) * kSkewHS : 0;
   // C in the caller's order: staging area, this lane's entries in it, offsets
   OutPasses<OM> op_at;
@@ -1143,13 +1147,16 @@ static hipError_t launch_skew_h(const E* A, const E* B, E* C, const IndexOp& op,
   SkewMap mp{};
   if (!skew_map(op, 4, 2, &mp)) return hipErrorInvalidValue;
   SkewMap q = mp;
-  switch (quad_mode(&q, 1)) {
+  switch (op.quad ? quad_mode(&q, 1) : kQuadNone) {
     case kQuadKK: return launch_skew_hn<NT, 4, kQuadKK, E>(A, B, C, op, q, maxslot, s, out);
     case kQuadKR: return launch_skew_hn<NT, 4, kQuadKR, E>(A, B, C, op, q, maxslot, s, out);
     case kQuadRK: return launch_skew_hn<NT, 4, kQuadRK, E>(A, B, C, op, q, maxslot, s, out);
     case kQuadRR: return launch_skew_hn<NT, 4, kQuadRR, E>(A, B, C, op, q, maxslot, s, out);
-    default: return launch_skew_hn<NT, 1, kQuadKK, E>(A, B, C, op, mp, maxslot, s, out);
+    default: break;
   }
+  if (mp.pos[0] == 0 && mp.pos[1] == 1)
+    return launch_skew_hn<NT, 4, kQuadNone, E>(A, B, C, op, mp, maxslot, s, out);
+  return launch_skew_hn<NT, 1, kQuadNone, E>(A, B, C, op, mp, maxslot, s, out);
 }
 
 template <typename E>
