@@ -823,7 +823,18 @@ int build_plan(PlanCore& P, std::string& err) {
           std::vector<int> p;
           for (int i = 0; i < nM; ++i) p.push_back(pos_in(La, MA[nM - 1 - i]));
           bool ok = make_runs(p, &gidx.aM);
-          const std::vector<int> Kg = half ? quad_order(La, K, 5) : K;
+          // 16-bit: the order that keeps neighbouring threads' loads together
+          // (quad_order), unless B holds [N, K] in A's order: a permute of B
+          // costs more than that order gains (FP16, 2^14 x 2^7 over 2^7: 17.3 us
+          // with the permute, 12.0 in A's order; 2^13 x 2^12 over 2^8: 96, 86)
+          std::vector<int> Bk = NB, Kb;
+          Bk.insert(Bk.end(), K.begin(), K.end());
+          const std::vector<int> Kg = half && Bk != Lb ? quad_order(La, K, 5) : K;
+          // B as [N, K] in another order: one permute either way, of A or of
+          // B.  A's below 2^20 entries, up to 2^13 rows and 2^6 terms (2^12 x 2^7 over
+          // 2^5 10.9 us permuting A, 11.8 B; 2^13 x 2^12 over 2^5 41.4, 44.7;
+          // 2^14 x 2^9 over 2^5 21.4, 19.7; 2^12 x 2^10 over 2^7 19.8, 18.4)
+          if (half && ra < 20 && nM <= 13 && nK <= 6 && Bk != Lb && k_low_block(Lb, Kb)) ok = false;
           p.clear();
           for (int i = 0; i < nK; ++i) p.push_back(pos_in(La, Kg[nK - 1 - i]));
           ok = ok && make_runs(p, &gidx.aK);
