@@ -191,6 +191,23 @@ bool skew_quad(const std::vector<int>& La, const std::vector<int>& Lb, const std
   return below(8) == 1 && nN <= 4 && (below(2) == 1 || ra < 28);
 }
 
+// Whether twice `sp` slabs are faster than sp for a GEMM of 2^nC outputs over
+// 2^nK terms in tiles of 2^tl: what a workgroup's shorter sum saves, in the
+// time that its terms take (measured on few workgroups: 20 us per 512 in
+// 128x128 tiles and 5.6 in 64x64 ones in 16-bit storage, 115 and 41 in
+// complex64; in 16-bit storage half of that where a CU has a workgroup already,
+// since two share its loads), against 16 bytes of write and read per output
+// and added slab and, from one slab, the launch that adds them.  FP16, 2^13 x 2^7
+// over 2^9: 22 us in one slab, 33 in two; 2^11 x 2^7 over 2^9 20 and 16.6; 2^14
+// x 2^7 over 2^10 38 in one, 40 in four; over 2^11 52 in two, 56 in four.
+bool split_pays(bool half, int tl, int nC, int nK, int sp) {
+  const double us_per_term = half ? (tl == 7 ? 0.030 : 0.011) : (tl == 7 ? 0.22 : 0.08);
+  const bool shared = half && ((int64_t)sp << (nC - 2 * tl)) >= 256;
+  const double saved = std::ldexp(us_per_term, nK) / (2 * sp) * (shared ? 0.5 : 1.0);
+  const double added = std::ldexp(16.0, nC) * (sp == 1 ? 2 : sp) / 5.2e6 + (sp == 1 ? 2.0 : 0.0);
+  return saved > added;
+}
+
 struct Buf {
   int64_t elems;
   int t0, t1;
@@ -908,9 +925,10 @@ int build_plan(PlanCore& P, std::string& err) {
         // and down to slabs of kSplitMinK terms while there are fewer than
         // two workgroups per CU (FP16, 256 x 128 outputs over 2^11 terms: 43
         // us in 2 slabs, 21 in 8; complex64, 4096 x 256 over 2^12: 276 us in
-        // 4, 249 in 8)
+        // 4, 249 in 8) and a slab's terms take longer than the slabs that are
+        // added take to write and read
         while (!fills && !P.lean && tiles * sp < (gather && nK < 11 ? 256 : 512) &&
-               ((int64_t)1 << nK) / (sp * 2) >= kSplitMinK && sp < 64)
+               ((int64_t)1 << nK) / (sp * 2) >= kSplitMinK && sp < 64 && split_pays(half, tl, nM + nN, nK, sp))
           sp *= 2;
         // with tuning, room for every split the tuner may try: slabs of at
         // least 256 along K, at most 64 slabs, workspace <= 2^28 entries,

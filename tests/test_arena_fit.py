@@ -15,6 +15,7 @@ from tests.plan_interp import PlanInterpreter  # noqa: E402
 # grid, cycles, open qubits: networks with one or two split GEMMs at the
 # arena's largest extent
 NETS = [(3, 6, 8, 16), (4, 4, 8, 16), (4, 5, 8, 16)]
+CASES = [(NETS[0], "c64"), (NETS[1], "c64"), (NETS[2], "c64"), (NETS[0], "f16s"), (NETS[1], "f16s")]
 
 
 def _net(rows, cols, cycles, n_open):
@@ -30,8 +31,7 @@ def _slab_terms(plan):
     return [o["K"] // o["split_k"] for o in plan.json()["ops"] if o["kind"] == 1 and o["split_k"] > 1]
 
 
-@pytest.mark.parametrize("dtype", ["c64", "f16s"])
-@pytest.mark.parametrize("net", NETS)
+@pytest.mark.parametrize("net,dtype", CASES)
 def test_fewer_slabs_in_a_smaller_budget(net, dtype):
     args = _net(*net)
     full = tnrcs.Plan(*args, dtype=dtype, dry_run=True)
@@ -58,8 +58,7 @@ def test_smaller_plan_has_the_same_value():
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("dtype", ["c64", "f16s"])
-@pytest.mark.parametrize("net", NETS)
+@pytest.mark.parametrize("net,dtype", CASES)
 def test_runs_in_the_smaller_workspace(net, dtype):
     print(f"smaller workspace {net} {dtype}", flush=True)
     args = _net(*net)
