@@ -381,20 +381,26 @@ __global__ __launch_bounds__(512, 1) void k_hgemm_pp(const E* __restrict__ A, co
 // per thread and stage) held the kernel to 730 complex TFLOP/s on the rank-27 x
 // rank-25 pair, 1010 with eight 8-byte stores.  The stage's K offset
 // moves by a carrying add restricted to A's K bits above 4 (in increasing
-// positions).  B is [N][K] and C is [M][N], as in k_hgemm; with W, slab z of
-// k_len terms goes there, unscaled in FP32.
+// positions).  B is [N][K] and C is [M][N], as in k_hgemm, or in the caller's
+// order (OM = OutMap), or (SlabOut) slab z of k_len terms goes to W, unscaled in FP32.
 struct GatherAH {
   SkewMap mp;
   Runs aM;
   uint64_t maskK = 0, incK = 0;
+};
+// (a type of its own: carried by the plain kernel, slabs had cost it 3 to 6 % of
+// short sums, 2^16 x 2^7 over 2^5 13.3 -> 14.1 us)
+struct SlabOut {
+  float2* W = nullptr;
+  int64_t k_len = 0;
   SlabMap slab{};
 };
 
 template <int MODE, typename H, typename E, typename OM>
 __global__ __launch_bounds__(256, 2) void k_hgemm_ga(const E* __restrict__ A, const E* __restrict__ B,
-                                                   E* __restrict__ C, float2* __restrict__ W, int64_t N, int64_t K,
-                                                   int64_t k_len, float out_scale, float* maxslot, int64_t Mt,
-                                                   int64_t Nt, const GatherAH g, const OM om) {
+                                                   E* __restrict__ C, int64_t N, int64_t K, float out_scale,
+                                                   float* maxslot, int64_t Mt, int64_t Nt, const GatherAH g,
+                                                   const OM om) {
   typedef typename Frag<H>::T F;
   constexpr int BK = 32, BM = 128, BN = 128, LDK = BK + 8, P = 2, WTM = 2, WTN = 2;
   constexpr int NVB = BK / (256 / BN) / 4;  // B: uint4 loads per thread per stage
@@ -429,11 +435,17 @@ __global__ __launch_bounds__(256, 2) void k_hgemm_ga(const E* __restrict__ A, co
   const int row0 = (1 << (MODE == kQuadKR ? g.mp.mb[1] : MODE == kQuadKK ? 0 : g.mp.mb[0])) * LDK;
   const int row1 = MODE == kQuadRR ? (1 << g.mp.mb[1]) * LDK : 0;
   const uint64_t abase = dep_u<12>((uint64_t)bm, g.aM);
-  uint64_t kofs = slab_offset(g.slab, z);
+  uint64_t kofs = 0;
+  int64_t k_len = K, kb = 0;  // this workgroup's terms, and the first
+  if constexpr (std::is_same<OM, SlabOut>::value) {
+    kofs = slab_offset(om.slab, z);
+    k_len = om.k_len;
+    kb = z * k_len;
+  }
   const int brow = tid / 2, bk = (tid % 2) * 16;
   int64_t brow_b = bn + brow;
   if constexpr (has_out<OM>) brow_b = (int64_t)dep((uint64_t)brow_b, om.nmap);
-  const uint4* Bp = reinterpret_cast<const uint4*>(B + brow_b * K + z * k_len + bk);
+  const uint4* Bp = reinterpret_cast<const uint4*>(B + brow_b * K + kb + bk);
   uint4 ra[4], rb[NVB];
   auto load_a = [&]() {
     const E* base = A + (abase + kofs);
@@ -564,10 +576,8 @@ __global__ __launch_bounds__(256, 2) void k_hgemm_ga(const E* __restrict__ A, co
     record_max_in(maxslot, mx, reinterpret_cast<float*>(&As[0][0][0][0]));
     return;
   }
-  // a loop of its own: a branch per store in the one below took the K = 64
-  // step of 2^24 rows from 2.79 to 3.15 ms
-  if (W) {
-    float2* Ws = W + z * (Mt * BM * N) + (bm + wm + 4 * kh) * N + bn + wn + c;
+  if constexpr (std::is_same<OM, SlabOut>::value) {
+    float2* Ws = om.W + z * (Mt * BM * N) + (bm + wm + 4 * kh) * N + bn + wn + c;
 #pragma unroll
     for (int i = 0; i < WTM; ++i)
 #pragma unroll
@@ -618,15 +628,19 @@ __global__ __launch_bounds__(256) void k_hsplit_sum(const float2* __restrict__ W
 }
 
 template <int MODE, typename H, typename E>
-static void hgemm_ga_launch(const E* A, const E* B, E* C, float2* W, int64_t M, int64_t N, int64_t K, int splits,
-                            float scale, float* maxslot, const GatherAH& g, const OutMap* out, hipStream_t s) {
+static void hgemm_ga_launch(const E* A, const E* B, E* C, int64_t M, int64_t N, int64_t K, const SlabOut& slabs,
+                            int splits, float scale, float* maxslot, const GatherAH& g, const OutMap* out,
+                            hipStream_t s) {
   const int64_t Mt = M / 128, Nt = N / 128;
   if (out)
-    hipLaunchKernelGGL((k_hgemm_ga<MODE, H, E, OutMap>), dim3((unsigned)(Mt * Nt)), dim3(256), 0, s, A, B, C, nullptr, N,
-                       K, K, scale, maxslot, Mt, Nt, g, *out);
+    hipLaunchKernelGGL((k_hgemm_ga<MODE, H, E, OutMap>), dim3((unsigned)(Mt * Nt)), dim3(256), 0, s, A, B, C, N, K,
+                       scale, maxslot, Mt, Nt, g, *out);
+  else if (splits > 1)
+    hipLaunchKernelGGL((k_hgemm_ga<MODE, H, E, SlabOut>), dim3((unsigned)(Mt * Nt * splits)), dim3(256), 0, s, A, B, C,
+                       N, K, scale, maxslot, Mt, Nt, g, slabs);
   else
-    hipLaunchKernelGGL((k_hgemm_ga<MODE, H, E, NoOut>), dim3((unsigned)(Mt * Nt * splits)), dim3(256), 0, s, A, B, C, W,
-                       N, K, K / splits, scale, maxslot, Mt, Nt, g, NoOut{});
+    hipLaunchKernelGGL((k_hgemm_ga<MODE, H, E, NoOut>), dim3((unsigned)(Mt * Nt)), dim3(256), 0, s, A, B, C, N, K,
+                       scale, maxslot, Mt, Nt, g, NoOut{});
 }
 
 template <typename H, typename E>
@@ -634,15 +648,16 @@ static hipError_t hgemm_ga_t(const E* A, const E* B, E* C, const IndexOp& idx, f
                              float2* W, int splits, const OutMap* out, hipStream_t s) {
   const int64_t M = (int64_t)1 << idx.nM, N = (int64_t)1 << idx.nN, K = (int64_t)1 << idx.nK;
   GatherAH g{};
-  if (!skew_map(idx, 5, 0, &g.mp) || g.mp.v != 12 || !slab_map(idx, splits, 5, &g.slab)) return hipErrorInvalidValue;
+  SlabOut slabs{W, K / std::max(splits, 1), {}};
+  if (!skew_map(idx, 5, 0, &g.mp) || g.mp.v != 12 || !slab_map(idx, splits, 5, &slabs.slab)) return hipErrorInvalidValue;
   g.aM = idx.aM;
   g.maskK = dep_host_h((uint64_t)(K - 1) & ~(uint64_t)31, idx.aK);
   g.incK = K > 32 ? dep_host_h(32, idx.aK) : 0;
   switch (quad_mode(&g.mp, 2)) {
-    case kQuadKK: hgemm_ga_launch<kQuadKK, H, E>(A, B, C, W, M, N, K, splits, scale, maxslot, g, out, s); break;
-    case kQuadKR: hgemm_ga_launch<kQuadKR, H, E>(A, B, C, W, M, N, K, splits, scale, maxslot, g, out, s); break;
-    case kQuadRK: hgemm_ga_launch<kQuadRK, H, E>(A, B, C, W, M, N, K, splits, scale, maxslot, g, out, s); break;
-    case kQuadRR: hgemm_ga_launch<kQuadRR, H, E>(A, B, C, W, M, N, K, splits, scale, maxslot, g, out, s); break;
+    case kQuadKK: hgemm_ga_launch<kQuadKK, H, E>(A, B, C, M, N, K, slabs, splits, scale, maxslot, g, out, s); break;
+    case kQuadKR: hgemm_ga_launch<kQuadKR, H, E>(A, B, C, M, N, K, slabs, splits, scale, maxslot, g, out, s); break;
+    case kQuadRK: hgemm_ga_launch<kQuadRK, H, E>(A, B, C, M, N, K, slabs, splits, scale, maxslot, g, out, s); break;
+    case kQuadRR: hgemm_ga_launch<kQuadRR, H, E>(A, B, C, M, N, K, slabs, splits, scale, maxslot, g, out, s); break;
     default: return hipErrorInvalidValue;
   }
   if (splits > 1)
