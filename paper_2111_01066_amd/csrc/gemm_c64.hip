@@ -188,6 +188,12 @@ __global__ __launch_bounds__(256, 2) void k_cgemm128(const float2* __restrict__ 
   float2* As = AB[0];
   float2* Bs = AB[1];
   auto swz = [](int k) { return (k & 8) << 1; };
+  // gathered A: its stores' lanes may differ in any k bits, so bits 0 (which a
+  // lane's reads do not change) and 1 move rows too; the planner gives
+  // the lanes' k bits the numbers 3, 0 and 1 first (swizzle_order).  With bit 3 alone A's
+  // with several k bits in their lowest positions were up to 14 % slower
+  // (2^14 x 2^9 over 2^11, k at positions 1 to 5: 896 us, 797 now)
+  auto swz_a = [&](int k) { return swz(k) ^ (GA != 0 ? (k & 1) << 3 ^ (k & 2) << 1 : 0); };
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int64_t tm, tn, z;
   xcd_tile(blockIdx.x, Mt, Nt, gridDim.x, tm, tn, z);
@@ -221,7 +227,7 @@ __global__ __launch_bounds__(256, 2) void k_cgemm128(const float2* __restrict__ 
     auto entry = [&](int e, uint64_t& off) {
       int m, k;
       skew_split(g.mp, e, off, m, k);
-      return (uint32_t)(k * LD + (m ^ swz(k)));
+      return (uint32_t)(k * LD + (m ^ swz_a(k)));
     };
     uint64_t off;
     uodd = entry(1, off);
@@ -285,8 +291,9 @@ __global__ __launch_bounds__(256, 2) void k_cgemm128(const float2* __restrict__ 
       }
   };
   // this lane's operands: rows wm + c and wm + 64 + c at k = kk + kh
-  const float2* a_lo = As + kh * LD + wm + c;
-  const float2* a_hi = As + kh * LD + ((wm + c) ^ 16);
+  const float2* a_at[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) a_at[q] = As + kh * LD + ((wm + c) ^ swz_a((q & 2) << 2 | (q & 1) << 1 | kh));
   const float2* b_lo = Bs + kh * LD + wn + c;
   const float2* b_hi = Bs + kh * LD + ((wn + c) ^ 16);
   bool first = true;
@@ -335,7 +342,7 @@ __global__ __launch_bounds__(256, 2) void k_cgemm128(const float2* __restrict__ 
       float a[P][2], b[P][2];
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        const float2 x = (kk < 8 ? a_lo : a_hi)[kk * LD + 64 * i], y = (kk < 8 ? b_lo : b_hi)[kk * LD + 64 * i];
+        const float2 x = a_at[(kk >> 2 & 2) | (kk >> 1 & 1)][kk * LD + 64 * i], y = (kk < 8 ? b_lo : b_hi)[kk * LD + 64 * i];
         a[0][i] = x.x;
         a[1][i] = x.y;
         b[0][i] = y.x;

@@ -148,6 +148,29 @@ std::vector<int> quad_order(const std::vector<int>& La, const std::vector<int>& 
   return out;
 }
 
+// K order for the complex64 GEMM that reads A in place, chunks of 16 k (its
+// lowest contracted bits) by 128 rows, 16-byte loads: K in A's order, but of
+// the chunk's k bits those that tell the lanes of a wave apart become k bits
+// 3, 0 and 1, for which the kernel's LDS rows are swizzled, so that a store's
+// lanes meet in few banks.
+std::vector<int> swizzle_order(const std::vector<int>& La, const std::vector<int>& MA, const std::vector<int>& K) {
+  const int n = (int)K.size();
+  if (n < 4 || MA.size() < 7) return K;
+  std::vector<int> chunk;  // positions of the chunk's bits
+  for (int i = 0; i < 4; ++i) chunk.push_back(pos_in(La, K[n - 1 - i]));
+  for (int i = 0; i < 7; ++i) chunk.push_back(pos_in(La, MA[MA.size() - 1 - i]));
+  std::sort(chunk.begin(), chunk.end());
+  std::vector<int> lanes, others;
+  for (int i = 0; i < 4; ++i) {
+    const int w = K[n - 1 - i], p = pos_in(La, w);
+    (p >= chunk[1] && p <= chunk[6] ? lanes : others).push_back(w);
+  }
+  lanes.insert(lanes.end(), others.begin(), others.end());
+  std::vector<int> out(K.begin(), K.end() - 4);
+  for (int i : {0, 3, 2, 1}) out.push_back(lanes[i]);  // k bits 3, 2, 1, 0
+  return out;
+}
+
 // Whether the lowest 8 bits of K (or all, if fewer) are the tensor's lowest, in order.
 bool k_aligned(const std::vector<int>& have, const std::vector<int>& K) {
   const int nK = (int)K.size();
@@ -846,7 +869,7 @@ int build_plan(PlanCore& P, std::string& err) {
           // with the permute, 12.0 in A's order; 2^13 x 2^12 over 2^8: 96, 86)
           std::vector<int> Bk = NB, Kb;
           Bk.insert(Bk.end(), K.begin(), K.end());
-          const std::vector<int> Kg = half && Bk != Lb ? quad_order(La, K, 5) : K;
+          const std::vector<int> Kg = Bk == Lb ? K : half ? quad_order(La, K, 5) : swizzle_order(La, MA, K);
           // B as [N, K] in another order: one permute either way, of A or of
           // B.  A's below 2^20 entries, up to 2^13 rows and 2^6 terms (2^12 x 2^7 over
           // 2^5 10.9 us permuting A, 11.8 B; 2^13 x 2^12 over 2^5 41.4, 44.7;
