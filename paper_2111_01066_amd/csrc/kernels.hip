@@ -1215,23 +1215,16 @@ __device__ double block_sum(double v) {
   return r;
 }
 
-__global__ __launch_bounds__(256) void k_norm2_part(const amp2* __restrict__ amp, int64_t n, double* part) {
-  double s[4] = {0, 0, 0, 0};  // four loads in flight per thread
-  const int64_t step = (int64_t)gridDim.x * blockDim.x;
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  for (; i + 3 * step < n; i += 4 * step) {
-    amp2 a[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) a[q] = amp[i + q * step];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) s[q] += a[q].x * a[q].x + a[q].y * a[q].y;
+// (One load per iteration: with four in flight by hand, 2^24 amplitudes took
+// 49 us instead of 44.)
+__global__ __launch_bounds__(256) void k_norm2_part(const double* __restrict__ amp, int64_t n, double* part) {
+  double s = 0;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+    const double re = amp[2 * i], im = amp[2 * i + 1];
+    s += re * re + im * im;
   }
-  for (; i < n; i += step) {
-    const amp2 a = amp[i];
-    s[0] += a.x * a.x + a.y * a.y;
-  }
-  const double t = block_sum((s[0] + s[1]) + (s[2] + s[3]));
-  if (threadIdx.x == 0) part[blockIdx.x] = t;
+  s = block_sum(s);
+  if (threadIdx.x == 0) part[blockIdx.x] = s;
 }
 
 __global__ __launch_bounds__(256) void k_xeb_part(const double* __restrict__ amp, int64_t n,
@@ -1268,7 +1261,7 @@ hipError_t launch_norm2(const double* amp, int64_t n, double* out, hipStream_t s
   double* part = nullptr;
   hipError_t e = hipMallocAsync((void**)&part, kRedBlocks * sizeof(double), s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_norm2_part, dim3(kRedBlocks), dim3(256), 0, s, (const amp2*)amp, n, part);
+  hipLaunchKernelGGL(k_norm2_part, dim3(kRedBlocks), dim3(256), 0, s, amp, n, part);
   hipLaunchKernelGGL(k_final_sum, dim3(1), dim3(256), 0, s, part, kRedBlocks, 1, out);
   e = hipGetLastError();
   hipError_t e2 = hipFreeAsync(part, s);
