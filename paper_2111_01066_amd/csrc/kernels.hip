@@ -552,8 +552,9 @@ hipError_t launch_generic(int dtype, const void* A, const void* B, void* C, cons
   }
   // several lanes per output while the outputs alone leave CUs without
   // threads (2^16 threads, one block per CU) and the sum has terms for them
+  // (a sum of two terms rounds less in one chain than as the sum of two lanes)
   const int lanes = std::min({6, op.nK, kGenericLanesLog2 - (op.nM + op.nN)});
-  if (lanes > 0) {
+  if (lanes > 0 && op.nK > 1) {
     const dim3 g((unsigned)std::max<int64_t>(1, (int64_t)1 << std::max(0, op.nM + op.nN + lanes - 8)));
     if (dtype == TN_DTYPE_F16S)
       hipLaunchKernelGGL(k_generic_lanes<cf16>, g, dim3(256), 0, s, (const cf16*)A, (const cf16*)B, (cf16*)C, op,

@@ -187,8 +187,9 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(const E* __restrict__ l
       } else if (lc >= 10 && op.nM >= 1 && op.nN >= 1) {
         mx = small_blocks<2, 2, E>(op, T, tm, tn, ka, kb, sc);
       } else {
-        // 2^L lanes share an output, lane t taking the terms t, t + 2^L, ...
-        const int L = max(0, min(min(6, op.nK), 8 - lc));
+        // 2^L lanes share an output, lane t taking the terms t, t + 2^L, ... (a
+        // sum of two terms rounds less in one chain than as the sum of two lanes)
+        const int L = op.nK > 1 ? max(0, min(min(6, op.nK), 8 - lc)) : 0;
         const int t = tid & ((1 << L) - 1);
         for (int i = tid; i < 1 << (lc + L); i += kSmallThreads) {
           const int c = i >> L;
