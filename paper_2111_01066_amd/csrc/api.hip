@@ -252,8 +252,15 @@ static int upload_scales(tn_plan_s* p) {
   return TN_OK;
 }
 
+// Bytes that the plan takes of a budget: a caller's workspace holds the arena
+// alone.
+static int64_t budget_bytes(const PlanCore& P) {
+  return ((P.opts.arena ? 0 : P.leaves_elems + P.bound_elems) + P.arena_elems) * (int64_t)elem_bytes_of(P.opts.dtype);
+}
+
 // Device copy of a small network's program, and behind it room for the results
-// of up to 4096 slices per launch (16 MiB at most), in one allocation.
+// of up to 4096 slices per launch (16 MiB at most, and what a caller's budget
+// leaves), in one allocation.
 static int upload_small(tn_plan_s* p) {
   const PlanCore& P = p->core;
   const SmallNet& S = P.small;
@@ -266,7 +273,11 @@ static int upload_small(tn_plan_s* p) {
   const size_t b_tabs = pad(S.tabs.size() * 2), b_ops = pad(S.ops.size() * sizeof(SmallOp)),
                b_leaves = pad(leaves.size() * sizeof(SmallLeaf));
   const int64_t n_amp = (int64_t)1 << P.accum.n_open;
-  p->small_slices = std::min<int64_t>({P.stats.n_slices, 4096, ((int64_t)1 << 21) / n_amp});
+  int64_t room = (int64_t)1 << 40;
+  if (!P.opts.arena && P.opts.arena_bytes > 0)
+    room = P.opts.arena_bytes - budget_bytes(P) - (int64_t)(b_tabs + b_ops + b_leaves) - 512;
+  p->small_slices = std::max<int64_t>(1, std::min<int64_t>({P.stats.n_slices, 4096, ((int64_t)1 << 21) / n_amp,
+                                                            room / (int64_t)(n_amp * sizeof(float2) + sizeof(double2))}));
   const int64_t ns = p->small_slices > 1 ? p->small_slices : 0;
   const size_t b_factors = pad((size_t)ns * sizeof(double2)), b_roots = pad((size_t)(ns * n_amp) * sizeof(float2));
   HIP_TRY(hipMalloc((void**)&p->d_small, b_tabs + b_ops + b_leaves + b_factors + b_roots), "alloc small network");
@@ -606,12 +617,6 @@ static int tune_classes(PlanCore& P, bool measure) {
   std::string err;
   int rc = build_plan(P, err);
   return rc ? fail(rc, "rebuild after class tuning: " + err) : TN_OK;
-}
-
-// Bytes that the plan takes of a budget: a caller's workspace holds the arena
-// alone.
-static int64_t budget_bytes(const PlanCore& P) {
-  return ((P.opts.arena ? 0 : P.leaves_elems + P.bound_elems) + P.arena_elems) * (int64_t)elem_bytes_of(P.opts.dtype);
 }
 
 // Plans again without the scratch that only gains speed when the plan would
