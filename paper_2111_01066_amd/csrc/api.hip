@@ -476,7 +476,7 @@ static int tune_plan(tn_plan_s* p) {
 constexpr int kFuseMaxK = 6;
 constexpr int64_t kClassTuneMaxBytes = (int64_t)48 << 30;
 constexpr int kGatherTuneLog2 = 22;
-constexpr int kGatherTuneMaxK = 16;  // nor on sums of 2^16 terms or more (one output per thread)
+constexpr int kGatherTuneMaxK = 16;  // nor on sums of 2^16 terms or more (at most 64 lanes per output)
 
 // Average time of one run of a one-step plan's ops in class `cls` (INFINITY
 // when the step does not fit the budget); builds, runs and frees the plan.
@@ -573,11 +573,11 @@ static int tune_classes(PlanCore& P, bool measure) {
   for (const PlanCore::StepInfo& st : P.steps) {
     const unsigned valid = step_classes(st.nM, st.nN, st.nK);
     std::vector<int> cand;
-    // the gathered kernel (one output per thread, operands re-read per
-    // output) is a candidate only for steps of at most 2^kGatherTuneLog2
-    // outputs and sums shorter than 2^kGatherTuneMaxK: beyond that it loses
-    // to every other class by far, and timing it would dominate the tuning
-    // time
+    // the gathered kernel (an output per thread, or per few lanes where they
+    // are fewer than 2^16; operands re-read per output) is a candidate only
+    // for steps of at most 2^kGatherTuneLog2 outputs and sums shorter than
+    // 2^kGatherTuneMaxK: beyond that it loses to every other class by far,
+    // and timing it would dominate the tuning time
     const bool big = st.nM + st.nN > kGatherTuneLog2 || st.nK >= kGatherTuneMaxK;
     if (valid & (1u << kOpGemm)) {
       if (st.nK > kFuseMaxK) continue;

@@ -23,7 +23,7 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 // 16 as (re, im) pairs; the next stage is loaded into registers while the
 // current one is multiplied.  With few workgroups per CU a stage's load
 // latency bounds it, with many the FP32 products: with planes in LDS and each
-// stage loaded where it was used, 3 x 1984 x 1088 x 1200 took 470 us (now 428),
+// stage loaded where it was used, 3 x 1984 x 1088 x 1200 took 465 us (now 403),
 // 192 x 320 x 2048 in 4 slabs 52 (37), 64 x 64 x 1024 80 (64).  Four waves per
 // SIMD: five spill and are no faster.
 
@@ -189,10 +189,10 @@ __global__ __launch_bounds__(256, 2) void k_cgemm128(const float2* __restrict__ 
   float2* Bs = AB[1];
   auto swz = [](int k) { return (k & 8) << 1; };
   // gathered A: its stores' lanes may differ in any k bits, so bits 0 (which a
-  // lane's reads do not change) and 1 move rows too; the planner gives
-  // the lanes' k bits the numbers 3, 0 and 1 first (swizzle_order).  With bit 3 alone A's
-  // with several k bits in their lowest positions were up to 14 % slower
-  // (2^14 x 2^9 over 2^11, k at positions 1 to 5: 896 us, 797 now)
+  // lane's reads do not change) and 1 move rows too; the planner gives the
+  // lanes' k bits the numbers 3, 0 and 1 first (swizzle_order).  With bit 3
+  // alone, A's with several k bits in their lowest positions were up to 14 %
+  // slower (2^14 x 2^9 over 2^11, k at positions 1 to 5: 896 us, 797 now)
   auto swz_a = [&](int k) { return swz(k) ^ (GA != 0 ? (k & 1) << 3 ^ (k & 2) << 1 : 0); };
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int64_t tm, tn, z;

@@ -388,8 +388,8 @@ struct GatherAH {
   Runs aM;
   uint64_t maskK = 0, incK = 0;
 };
-// (a type of its own: carried by the plain kernel, slabs had cost it 3 to 6 % of
-// short sums, 2^16 x 2^7 over 2^5 13.3 -> 14.1 us)
+// (A type of its own: carried by the plain kernel, slabs had cost it 3 to 6 %
+// of short sums, 2^16 x 2^7 over 2^5 13.3 -> 14.1 us.)
 struct SlabOut {
   float2* W = nullptr;
   int64_t k_len = 0;

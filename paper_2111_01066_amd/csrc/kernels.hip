@@ -420,8 +420,8 @@ __global__ __launch_bounds__(256) void k_generic(const E* __restrict__ A, const 
 // the terms t, t + 2^L, ..., and add their sums by butterfly.  With one
 // output per thread a step of 2^7 outputs over 2^11 terms was 128 serial
 // chains of dependent gathers (359 us, 18 us now).  A lane's terms are
-// gathered four at a time; the offsets of its first kGenTab / 2^L terms per
-// operand come from an LDS table as in k_generic.
+// gathered four at a time; the offsets of each 2^kTabBits terms' low bits come
+// from an LDS table per operand, as in k_generic.
 template <typename E>
 __global__ __launch_bounds__(256) void k_generic_lanes(const E* __restrict__ A, const E* __restrict__ B,
                                                       E* __restrict__ C, const IndexOp op, int L, float* maxslot) {

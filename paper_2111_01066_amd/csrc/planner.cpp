@@ -184,20 +184,22 @@ bool k_aligned(const std::vector<int>& have, const std::vector<int>& K) {
 // * nK >= 7: four k together (FP16, 2^21 to 2^24 rows over 2^7 terms: 0.6 to
 //   0.97 of the time), unless that order alone makes a permute of B
 //   necessary (of 2^12 entries or more) and A is below 2^27 entries: the
-//   permute's 4 to 5 us are more than is gained (2^10 rows x 2^5 over 2^8:
-//   15.7 us entry by entry, 19.5 us; 2^19 x 2^5 over 2^8: 127 and 118).
+//   permute's 4 to 5 us are more than is gained (2^10 x 2^5 over 2^8: 15.7 us
+//   entry by entry, 19.5 us; 2^19 x 2^5 over 2^8: 127 and 118).
 // * nK = 6: four k together (0.6 to 1.0 of the time).
 // * nK = 4, 5: four k together where the stores bound the step.  A narrow
-//   store hits each LDS bank eight times when the lowest 8 bits of A (2 within a
-//   load, 6 across the lanes of a wave) are rows: 2^22 x 2^5 over 2^4 193 us,
-//   165 with the wide ones; 2^23 x 2^4 over 2^5 560, 355.  With one k bit there
-//   it does so up to 16 columns (2^20 x 2^4 over 2^5 0.91 of the time), less in large
-//   tensors when that bit is a lane's (2^26 x 2^4 over 2^4 1.92 ms, 2.04).  With more
-//   the wide stores win where A is small enough for the caches (0.92 to
-//   0.99 of the time below 2^24 entries over 2^4 terms, below 2^18 over 2^5) and over 2^4 terms into
-//   up to 8 columns (2^21 x 2^3 123 us, 107); in larger steps the narrow ones are
-//   hidden behind the loads, and the wide ones, though fewer, made the whole step slower (2^25 x
-//   2^4 over 2^4 0.91 ms, 1.06; 2^26 x 2^4 over 2^5 2.53, 2.93).
+//   store hits each LDS bank eight times when the lowest 8 bits of A (2
+//   within a load, 6 across the lanes of a wave) are rows: 2^22 x 2^5 over
+//   2^4 193 us, 165 with the wide ones; 2^23 x 2^4 over 2^5 560, 355.  With
+//   one k bit there it does so up to 16 columns (2^20 x 2^4 over 2^5: 0.91 of
+//   the time), in large tensors only when that bit lies within a load (a
+//   lane's: 2^26 x 2^4 over 2^4 1.92 ms narrow, 2.04 wide).  With more, the
+//   wide stores win where A is small (0.92 to 0.99 of the time below 2^24
+//   entries over 2^4 terms, below 2^18 over 2^5) and over 2^4 terms into up to
+//   8 columns (2^21 x 2^3: 123 us, 107).  In larger steps the narrow ones are
+//   hidden behind the loads, and the wide ones, though fewer, made the whole
+//   step slower (2^25 x 2^4 over 2^4 0.91 ms, 1.06; 2^26 x 2^4 over 2^5 2.53,
+//   2.93).
 bool skew_quad(const std::vector<int>& La, const std::vector<int>& Lb, const std::vector<int>& K,
                const std::vector<int>& Kq, int nN, bool lean) {
   const int nK = (int)K.size();
@@ -215,14 +217,15 @@ bool skew_quad(const std::vector<int>& La, const std::vector<int>& Lb, const std
 }
 
 // Whether twice `sp` slabs are faster than sp for a GEMM of 2^nC outputs over
-// 2^nK terms in tiles of 2^tl: what a workgroup's shorter sum saves, in the
+// 2^nK terms in tiles of 2^tl.  What a workgroup's shorter sum saves, in the
 // time that its terms take (measured on few workgroups: 20 us per 512 in
 // 128x128 tiles and 5.6 in 64x64 ones in 16-bit storage, 115 and 41 in
-// complex64; in 16-bit storage half of that where a CU has a workgroup already,
-// since two share its loads), against 16 bytes of write and read per output
-// and added slab and, from one slab, the launch that adds them.  FP16, 2^13 x 2^7
-// over 2^9: 22 us in one slab, 33 in two; 2^11 x 2^7 over 2^9 20 and 16.6; 2^14
-// x 2^7 over 2^10 38 in one, 40 in four; over 2^11 52 in two, 56 in four.
+// complex64; in 16-bit storage half of that where a CU has a workgroup
+// already, since two share its loads), against 16 bytes of write and read per
+// output and added slab and, from one slab, the launch that adds them.  FP16,
+// 2^13 x 2^7 over 2^9: 22 us in one slab, 33 in two; 2^11 x 2^7 over 2^9 20
+// and 16.6; 2^14 x 2^7 over 2^10 38 in one, 40 in four; over 2^11 52 in two,
+// 56 in four.
 bool split_pays(bool half, int tl, int nC, int nK, int sp) {
   const double us_per_term = half ? (tl == 7 ? 0.030 : 0.011) : (tl == 7 ? 0.22 : 0.08);
   const bool shared = half && ((int64_t)sp << (nC - 2 * tl)) >= 256;

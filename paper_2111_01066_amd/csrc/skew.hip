@@ -509,7 +509,7 @@ struct SkewHalf<cbf16> {
 // further), by QuadMode: the loads of kQuadKR and kQuadRK differ in k1, so
 // they hold four k of two rows; those of kQuadRR differ in k0: two k of four
 // rows.  (Sixteen 2-byte stores per thread and chunk instead of four to eight
-// wider ones held the K = 512 step of 2^20 rows to 2.0 TB/s; 3.4 now.)
+// wider ones held the K = 512 step of 2^20 rows to 2.0 TB/s; 3.2 now.)
 // kQuadNone stores them one by one: the planner's choice (op.quad) where the
 // wide stores measured slower.
 template <int VEC, int MODE, int LPT, typename E, typename H>
