@@ -434,7 +434,6 @@ hipError_t launch_gemm_c64(const float2* A, const float2* B, float2* C, int64_t 
   if (splits < 1) splits = 1;
   const bool fits128 = (M % 128 == 0) && (N % 128 == 0);
   if (tile == 128 && !fits128) return hipErrorInvalidValue;
-  if (tile == 64 && splits > 1) return hipErrorInvalidValue;
   const bool big = fits128 && tile != 64;
   const int chunk = kAccChain / 16;  // K stages of the 128x128 kernel per FP32 chain
   if (splits > 1) {
