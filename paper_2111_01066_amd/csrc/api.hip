@@ -1179,6 +1179,7 @@ int tn_contract_batch(const tn_plan_t* plans, const int64_t* ranges, void* const
 int tn_plan_profile(tn_plan_t p, int64_t slice, void* amp, void* stream, float* op_ms, int32_t cap,
                     int32_t* n_ops) {
   if (!p || !amp || !n_ops) return fail(TN_E_ARG, "NULL argument");
+  if (p->core.pair_mode) return fail(TN_E_ARG, "pairwise plan: no slices to profile");
   if (p->core.opts.dry_run) return fail(TN_E_UNSUPPORTED, "dry-run plan has no device state");
   const PlanCore& P = p->core;
   const int nk = (int)P.ops.size() + 1;
