@@ -196,22 +196,22 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(const E* __restrict__ l
           const E* A = T + op.a + tm[c >> op.nN];
           const E* B = T + op.b + tn[c & ((1 << op.nN) - 1)];
           float re = 0.f, im = 0.f;
-          auto madd = [&](int k, float& r, float& s) {
+          auto madd = [&](int k, float& pr, float& pi) {
             const float2 x = to_f2(A[ka[k]]), y = to_f2(B[kb[k]]);
-            r = fmaf(x.x, y.x, r);
-            r = fmaf(-x.y, y.y, r);
-            s = fmaf(x.x, y.y, s);
-            s = fmaf(x.y, y.x, s);
+            pr = fmaf(x.x, y.x, pr);
+            pr = fmaf(-x.y, y.y, pr);
+            pi = fmaf(x.x, y.y, pi);
+            pi = fmaf(x.y, y.x, pi);
           };
           if (K >> L < 4) {
             for (int k = t; k < K; k += 1 << L) madd(k, re, im);
           } else {
             SumTree sum;
             for (int k = t, g = 1; k < K; k += 4 << L, ++g) {
-              float r = 0.f, s = 0.f;
+              float pr = 0.f, pi = 0.f;
 #pragma unroll
-              for (int q = 0; q < 4; ++q) madd(k + (q << L), r, s);
-              sum.add(r, s, g);
+              for (int q = 0; q < 4; ++q) madd(k + (q << L), pr, pi);
+              sum.add(pr, pi, g);
             }
             sum.total(re, im);
           }
